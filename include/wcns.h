@@ -333,8 +333,8 @@ wcns_status wcns_probe_copy(const double* src, double* dst, int64_t n, void* str
    arrays of doubles, owned by the caller), so that their error bounds can be
    checked against a reference: e^z through the 2^(k/64) table (Tang's
    method, |z| <= 708), e^z by Cody-Waite reduction and a degree-13 Taylor
-   polynomial (|z| <= 708), 1/x with two and with one Newton step from the
-   hardware seed (x normal), and the square root of 0 or of x in
+   polynomial (|z| <= 708), 1/x to full precision and with one Newton step
+   from the hardware seed (x normal), and the square root of 0 or of x in
    [2^-760, inf).  These are the exponentials, reciprocals and square roots
    of the residual (Sec. 2, eq. 20; the Roe average and the fluxes).
    WCNS_EINVAL for a NULL pointer, n < 0 or an unknown fn. */

@@ -155,12 +155,11 @@ void interp_params(const wcns_desc* d, InterpParams* ip) {
         b += softplus(2.0 * d->xi * ((m == i ? 1.0 : 0.0) - nu[first[m] + j]));
     B = std::max(B, b);
   }
-  // The fast path also takes the third map's exponential as
-  // Ke / (E_0 E_1): E_0 E_1 = exp(2 xi (w_0 + w_1 - c_0 - c_1)) must stay a
-  // normal number for w_0 + w_1 in [0, 1].
+  // The adjoint takes the third map's exponential as Ke / (E_0 E_1): E_0 E_1
+  // = exp(2 xi (w_0 + w_1 - c_0 - c_1)) must stay a normal number for
+  // w_0 + w_1 in [0, 1].
   const bool prod_ok = 2.0 * d->xi < 650.0 && 2.0 * d->xi * (c[0] + c[1]) < 650.0 &&
                        std::fabs(2.0 * d->xi * (1.0 - c[0] - c[1] - c[2])) < 650.0;
-  ip->fast_fe = (ip->shared_exp && B < 600.0 && prod_ok) ? 1 : 0;
   for (int m = 0; m < 3; ++m) {
     ip->C2[m] = ip->shared_exp ? 2.0 * d->xi * c[m] : 0.0;
     for (int j = 0; j < count[m]; ++j) {
@@ -169,10 +168,47 @@ void interp_params(const wcns_desc* d, InterpParams* ip) {
     }
   }
   ip->Ke = ip->shared_exp ? std::exp(2.0 * d->xi - ip->C2[0] - ip->C2[1] - ip->C2[2]) : 0.0;
-  // Polynomial coefficients of the maps in E (fe_map_poly), in long double
-  // from the K_j: elementary symmetric polynomials e_r of the map's K_j for
-  // the denominator prod_j (1 + E K_j), and of the K_l, l != j, weighted by
-  // -2 a_j and -2 b_j for the numerator.
+  ip->fast_fe = (ip->shared_exp && B < 600.0 && prod_ok) ? 1 : 0;
+  ip->xa = 0.0;
+  ip->xsh = 0;
+  std::fill(ip->Pd, ip->Pd + 10, 0.0);
+  std::fill(ip->Pa, ip->Pa + 7, 0.0);
+  std::fill(ip->Pb, ip->Pb + 7, 0.0);
+  if (!ip->fast_fe) return;
+  // The maps' variables and polynomials (InterpParams, fe_map_poly), in long
+  // double with the steepness that the rounded xa stands for.
+  const long double ln2 = std::log(2.0L);
+  ip->xa = (double)(2.0L * d->xi * 64.0L / ln2);
+  const long double x2 = (long double)ip->xa * ln2 / 64.0L;
+  // ln of the product of the three denominators at xsh = 0: largest at a
+  // vertex of the simplex, and above the sum of the three maps' own least
+  // values (at w_0 = 0, w_1 = 0, w_2 = 1); every denominator term carries
+  // 2^-xsh or 2^-2xsh, 3 + 4 + 2 * 3 = 13 of them in all.
+  auto ln_sum = [&](long double w, long double n) {  // ln(e^(x2 w) + e^(x2 n))
+    return x2 * std::max(w, n) + std::log1p(std::exp(-x2 * std::fabs(w - n)));
+  };
+  long double top = -1e30L, low = 0.0L;
+  for (int v = 0; v < 3; ++v) {
+    long double t = 0.0L;
+    for (int m = 0; m < 3; ++m)
+      for (int j = 0; j < count[m]; ++j) {
+        const long double w = m == v ? 1.0L : 0.0L, n = nu[first[m] + j];
+        t += m < 2 ? ln_sum(w, n) : ln_sum(1.0L - w, 1.0L - n);
+      }
+    top = std::max(top, t);
+  }
+  for (int m = 0; m < 3; ++m)
+    for (int j = 0; j < count[m]; ++j) {
+      const long double n = nu[first[m] + j];
+      low += m < 2 ? ln_sum(0.0L, n) : ln_sum(0.0L, 1.0L - n);
+    }
+  const long double shift = std::rint((top + low) / (26.0L * ln2));
+  if (!(top - 13.0L * shift * ln2 < 600.0L && low - 13.0L * shift * ln2 > -600.0L &&
+        shift * ln2 < 600.0L && x2 - 2.0L * shift * ln2 < 600.0L && shift >= 0.0L)) {
+    ip->fast_fe = 0;  // (implied by the conditions above for every null-point table in use)
+    return;
+  }
+  ip->xsh = (int)shift;
   const double* fa[3] = {ip->weno ? kV0a : kG0a, ip->weno ? kV1a : kG1a, ip->weno ? kV2a : kG2a};
   const double* fb[3] = {ip->weno ? kV0b : kG0b, ip->weno ? kV1b : kG1b, ip->weno ? kV2b : kG2b};
   const int offd[3] = {0, 3, 7}, offp[3] = {0, 2, 5};
@@ -184,27 +220,28 @@ void interp_params(const wcns_desc* d, InterpParams* ip) {
   };
   for (int m = 0; m < 3; ++m) {
     const int nt = count[m];
-    long double K[4], e[5], ex[5], pa[4] = {0, 0, 0, 0}, pb[4] = {0, 0, 0, 0};
-    for (int j = 0; j < nt; ++j) K[j] = ip->shared_exp ? (long double)ip->K[first[m] + j] : 0.0L;
-    esym(K, nt, e);
-    // monic: divided by the leading coefficient prod_j K_j (1 up to rounding)
-    const long double lead = ip->shared_exp ? e[nt] : 1.0L;
-    for (int r = 1; r < nt; ++r) ip->Pd[offd[m] + r - 1] = (double)(e[r] / lead);
-    ip->Pd[offd[m] + nt - 1] = (double)(1.0L / lead);
+    long double k[4], e[5], ex[5], pa[3] = {0, 0, 0}, pb[3] = {0, 0, 0};
+    for (int j = 0; j < nt; ++j) {
+      const long double n = nu[first[m] + j];
+      k[j] = m < 2 ? std::exp(x2 * n - shift * ln2) : std::exp(x2 * (1.0L - n) - 2.0L * shift * ln2);
+    }
+    esym(k, nt, e);
+    for (int r = 1; r <= nt; ++r) ip->Pd[offd[m] + r - 1] = (double)e[r];
     for (int j = 0; j < nt; ++j) {
       long double rest[3];
       int n = 0;
       for (int l = 0; l < nt; ++l)
-        if (l != j) rest[n++] = K[l];
+        if (l != j) rest[n++] = k[l];
       esym(rest, n, ex);
-      for (int r = 1; r < nt; ++r) {
-        pa[r] += -2.0L * fa[m][j] * ex[r];
-        pb[r] += -2.0L * fb[m][j] * ex[r];
+      for (int r = 0; r < nt - 1; ++r) {  // the coefficient of X^(r + 1)
+        const long double t = m < 2 ? k[j] * ex[nt - 2 - r] : ex[nt - 1 - r];
+        pa[r] += -2.0L * fa[m][j] * t;
+        pb[r] += -2.0L * fb[m][j] * t;
       }
     }
-    for (int r = 1; r < nt; ++r) {
-      ip->Pa[offp[m] + r - 1] = (double)(pa[r] / lead);
-      ip->Pb[offp[m] + r - 1] = (double)(pb[r] / lead);
+    for (int r = 0; r < nt - 1; ++r) {
+      ip->Pa[offp[m] + r] = (double)pa[r];
+      ip->Pb[offp[m] + r] = (double)pb[r];
     }
   }
 }

@@ -20,7 +20,7 @@
 //  * the projection uses the sparsity of the Euler eigenvectors: one shared
 //    scalar theta = b2*rho - b1*(u.m) + b1*E per node instead of a dense
 //    nv x nv product;
-//  * reciprocals are v_rcp_f64 refined by two Newton steps;
+//  * reciprocals are v_rcp_f64 refined by one third-order step;
 //  * tanh returns +-1 without evaluation once |x| >= 20 (tanh(x) rounds to
 //    +-1 in FP64 for |x| > 19.06), which at large steepness xi covers almost
 //    every call.
@@ -54,16 +54,20 @@ struct InterpParams {
   //   shared_exp = 0:  K[j] = nu_j                      (C2 unused)
   double K[10];
   double C2[3];
-  double Ke;        // exp(2 xi - C2[0] - C2[1] - C2[2]) (shared_exp; weigh5)
-  // fe_map_poly (shared_exp): per map m with NT_m terms, prod_j D_j and the
-  // two parts of sum_j -2 A_j(w) prod_{l != j} D_l, alpha (constant in w)
-  // and beta (times w), D_j = 1 + E K_j, as polynomials in E divided by the
-  // leading coefficient prod_j K_j (= 1 up to rounding: c_m is the mean of
-  // the map's null points), so that the denominator is monic:
-  //   Pd = [c_1 .. c_{NT-1}, c_0] for E^NT + c_{NT-1} E^{NT-1} + .. + c_0,
-  //   Pa, Pb = the coefficients of E^1 .. E^{NT-1} (the constants vanish);
+  double Ke;        // exp(2 xi - C2[0] - C2[1] - C2[2]) (shared_exp; the adjoint)
+  // fe_map_poly (fast_fe).  X_0 = 2^-xsh e^(2 xi w_0), X_1 = 2^-xsh e^(2 xi
+  // w_1) and X_2 = X_0 X_1 = 2^-2xsh e^(2 xi (1 - w_2)) are the variables of
+  // the three maps; term j of map m is saturated to one side or the other as
+  // X_m is far above or below k_j = 2^-xsh e^(2 xi nu_j) (m = 0, 1) or
+  // 2^-2xsh e^(2 xi (1 - nu_j)) (m = 2).  Per map with NT terms:
+  //   Pd = [c_{NT-1}, .., c_0] of prod_j (X + k_j) = X^NT + c_{NT-1} X^{NT-1} + .. ;
+  //   Pa, Pb = the coefficients of X^1 .. X^{NT-1} of the two parts of
+  //     g prod_j (X + k_j) - w prod_j (X + k_j), constant in w and times w
+  //     (the coefficients of X^0 vanish);
   // maps at offsets 0, 3, 7 of Pd and 0, 2, 5 of Pa and Pb
   double Pd[10], Pa[7], Pb[7];
+  double xa;        // 2 xi 64 / ln 2 (exp2_tab)
+  int xsh;          // the shift of X_0 and X_1 (fast_fe)
   int weights;      // WJS .. WLIN
   int zpow;         // exponent p of eq. 14 (1..4)
   int shared_exp;   // 1: one exponential per map (xi * max|nu - c| < 300)
@@ -79,13 +83,23 @@ struct PhysParams {
   int charproj;     // 1 = characteristic projection
 };
 
+// 1/x from the hardware seed r (relative error e, at most 2^-24.4) by one
+// third-order step r (1 + e + e^2), whose truncation e^3 is below 2^-73: as
+// exact as the two Newton steps r (1 + e) (1 + e^2) it replaces (0.5 ulp
+// measured for either), with one operation fewer and a shorter chain.
+// NEWTON2 keeps those two steps, for the weight statistics: they count
+// weights in bins, where a last-bit difference would move a count.
+template <bool NEWTON2 = false>
 __device__ __forceinline__ double rcp(double x) {
   double r = __builtin_amdgcn_rcp(x);
   double e = __builtin_fma(-x, r, 1.0);
-  r = __builtin_fma(r, e, r);
-  e = __builtin_fma(-x, r, 1.0);
-  r = __builtin_fma(r, e, r);
-  return r;
+  if constexpr (NEWTON2) {
+    r = __builtin_fma(r, e, r);
+    e = __builtin_fma(-x, r, 1.0);
+    return __builtin_fma(r, e, r);
+  }
+  e = __builtin_fma(e, e, e);
+  return __builtin_fma(r, e, r);
 }
 // 1/x with one Newton step: the seed's relative error (at most 2^-24.4)
 // squared, 2^-48.8 (about 10 ulp), for reciprocals whose error reaches the
@@ -97,22 +111,27 @@ __device__ __forceinline__ double rcp1(double x) {
 }
 
 // sqrt(x) for x = 0 or 2^-760 <= x < inf (densities, pressures, sound speeds
-// squared): v_rsq_f64 seed, one Goldschmidt step for sqrt and 1/(2 sqrt),
-// two Newton corrections of the root (about 1 ulp); NaN for x < -2^-1000.
-// Without the rescaling that a full-range square root needs for tiny
-// arguments.  The seed is taken at x + 2^-1000, which is x itself from
-// 2^-760 up and keeps x = 0 off the seed's pole: there every step below
-// gives g = 0 exactly, with no select.
+// squared): v_rsq_f64 seed, one Goldschmidt step (error below 2^-46), one
+// Newton correction of the root, whose residual is exact up to 2^-70: 0.5
+// ulp, like the two corrections and the refined 1/(2 sqrt) it had before
+// (three operations more); NaN for x < -2^-1000.  Without the rescaling that
+// a full-range square root needs for tiny arguments.  The seed is taken at
+// x + 2^-1000, which is x itself from 2^-760 up and keeps x = 0 off the
+// seed's pole: there every step below gives g = 0 exactly, with no select.
+// NEWTON2: the earlier form, bit for bit (weight statistics, see rcp).
+template <bool NEWTON2 = false>
 __device__ __forceinline__ double sqrt_pos(double x) {
   const double y = __builtin_amdgcn_rsq(x + 0x1p-1000);
   double g = x * y, h = 0.5 * y;
   const double r = __builtin_fma(-h, g, 0.5);
   g = __builtin_fma(g, r, g);
-  h = __builtin_fma(h, r, h);
+  if constexpr (NEWTON2) h = __builtin_fma(h, r, h);
   double d = __builtin_fma(-g, g, x);
   g = __builtin_fma(d, h, g);
-  d = __builtin_fma(-g, g, x);
-  g = __builtin_fma(d, h, g);
+  if constexpr (NEWTON2) {
+    d = __builtin_fma(-g, g, x);
+    g = __builtin_fma(d, h, g);
+  }
   return g;
 }
 
@@ -191,13 +210,50 @@ __device__ __forceinline__ double exp_tab(double z, const double* T) {
   return __builtin_ldexp(__builtin_fma(t, p, t), ni >> 6);
 }
 
+// Entry k of the table that exp2_tab reads (in LDS): 2^(k/64 - xsh) with k's
+// own contribution to the exponent, (k << 14) in the high word, taken off.
+__device__ __forceinline__ double exp2_tab_entry(int k, int xsh) {
+  const unsigned long long t = __builtin_bit_cast(unsigned long long, kExp2Tab64[k]);
+  return __builtin_bit_cast(double, t - ((unsigned long long)(unsigned)((k << 14) + (xsh << 20)) << 32));
+}
+
+// X = 2^(w a / 64 - xsh), w in [0, 1], for the FE maps: a = 2 xi 64 / ln 2, so
+// X = 2^-xsh e^(2 xi w).  w a = n + f with n an integer, f exact but for one
+// rounding of its own size (both from fused products, so no reduction in two
+// parts is needed), 2^(f/64) - 1 for |f| <= 1/2 by a degree-4 polynomial, and
+// 2^(n/64) from the table: its high word plus n << 14 carries n / 64 into the
+// exponent, with no separate scaling.  Relative error at most 2.7e-15 (the
+// polynomial's, economised in the Chebyshev sense from degree 5); the
+// rounding of w alone moves X by 2 xi 2^-53 = 2e-14, and the interpolated
+// value's error is the same to two digits with degree 5 (2.2e-16).
+__device__ __forceinline__ double exp2_tab(double w, double a, const double* T) {
+  constexpr double c1 = 0x1.62e42fefa0352p-7, c2 = 0x1.ebfbdff82c58fp-15;
+  constexpr double c3 = 0x1.c6b0c40d89cedp-23, c4 = 0x1.3b2ab6fba4e77p-31;
+  constexpr double kShift = 0x1.8p52;
+  const double sh = __builtin_fma(w, a, kShift);
+  const double n = sh - kShift;
+  const double f = __builtin_fma(w, a, -n);
+  const unsigned ni = (unsigned)__builtin_bit_cast(unsigned long long, sh);
+  // (words, so that the compiler adds to the high one alone)
+  using words = unsigned __attribute__((ext_vector_type(2)));
+  words e = __builtin_bit_cast(words, T[ni & 63]);
+  e.y += ni << 14;
+  const double t = __builtin_bit_cast(double, e);
+  double p = __builtin_fma(c4, f, c3);
+  p = __builtin_fma(p, f, c2);
+  p = __builtin_fma(p, f, c1);
+  p *= f;
+  return __builtin_fma(t, p, t);
+}
+
 // tanh(x) = sign(x) (1 - e^{-2|x|}) / (1 + e^{-2|x|}); +-1 for |x| >= 20.
+template <bool NEWTON2 = false>
 __device__ __forceinline__ double tanh_sat(double x) {
   const double ax = __builtin_fabs(x);
   double r = 1.0;
   if (ax < 20.0) {
     const double e = exp_cw(-2.0 * ax);
-    r = (1.0 - e) * rcp(1.0 + e);
+    r = (1.0 - e) * rcp<NEWTON2>(1.0 + e);
   }
   return __builtin_copysign(r, x);
 }
@@ -218,7 +274,7 @@ constexpr double D0 = 1.0 / 16.0, D1 = 10.0 / 16.0, D2 = 5.0 / 16.0;
 // E and E K_j stay finite and normal whenever a term is unsaturated as long
 // as xi |nu_j - c| < 300 (shared_exp); beyond that each unsaturated term
 // takes its own exponential.  If dg is not null it receives g'(w).
-template <int NT, int SPEC>
+template <int NT, int SPEC, bool NEWTON2 = false>
 __device__ __forceinline__ double fe_map(double w, const double (&a)[NT], const double (&b)[NT],
                                          const double* K, double C2, const InterpParams& P,
                                          double* dg) {
@@ -234,9 +290,9 @@ __device__ __forceinline__ double fe_map(double w, const double (&a)[NT], const 
     if (shared) {
       const double q = E * K[j];
       t = (q > 1.0) ? 1.0 : -1.0;
-      if (q > kQlo && q < kQhi) t = (q - 1.0) * rcp(q + 1.0);
+      if (q > kQlo && q < kQhi) t = (q - 1.0) * rcp<NEWTON2>(q + 1.0);
     } else {
-      t = tanh_sat(P.xi * (w - K[j]));
+      t = tanh_sat<NEWTON2>(P.xi * (w - K[j]));
     }
     const double A = b[j] == 0.0 ? a[j] : __builtin_fma(b[j], w, a[j]);
     g = __builtin_fma(A, t, g);
@@ -271,121 +327,124 @@ constexpr bool kMapSumsVanish = map_sums_vanish(kG0a, kG0b, 3) &&
                                 map_sums_vanish(kG2a, kG2b, 3);
 static_assert(kMapSumsVanish, "the FE maps' A_j must sum to zero");
 
-template <int SPEC = SPEC_GENERIC>
+template <int SPEC = SPEC_GENERIC, bool NEWTON2 = false>
 __device__ __forceinline__ double fe_g0(double w, const InterpParams& P, double* dg = nullptr) {
-  return fe_map<3, SPEC>(w, kG0a, kG0b, P.K, P.C2[0], P, dg);
+  return fe_map<3, SPEC, NEWTON2>(w, kG0a, kG0b, P.K, P.C2[0], P, dg);
 }
-template <int SPEC = SPEC_GENERIC>
+template <int SPEC = SPEC_GENERIC, bool NEWTON2 = false>
 __device__ __forceinline__ double fe_g1(double w, const InterpParams& P, double* dg = nullptr) {
-  return fe_map<4, SPEC>(w, kG1a, kG1b, P.K + 3, P.C2[1], P, dg);
+  return fe_map<4, SPEC, NEWTON2>(w, kG1a, kG1b, P.K + 3, P.C2[1], P, dg);
 }
-template <int SPEC = SPEC_GENERIC>
+template <int SPEC = SPEC_GENERIC, bool NEWTON2 = false>
 __device__ __forceinline__ double fe_g2(double w, const InterpParams& P, double* dg = nullptr) {
-  return fe_map<3, SPEC>(w, kG2a, kG2b, P.K + 7, P.C2[2], P, dg);
+  return fe_map<3, SPEC, NEWTON2>(w, kG2a, kG2b, P.K + 7, P.C2[2], P, dg);
 }
 
 // g(w) of one map in the form used by the forward SPEC_FE path.  With
-// t_j = tanh(xi (w - nu_j)) = 1 - 2 / D_j, D_j = 1 + q_j, q_j = E K_j:
-//   g(w) = w + sum_j A_j(w) - 2 sum_j A_j(w) / D_j,
-// taken over the common denominator prod_j D_j: the map returns the
-// numerator and leaves the denominator in *den, so that the caller can
-// normalise the three maps with one reciprocal.  The D_j are not clamped:
-// ln prod_j D_j is convex in w, so over the simplex of (w_0, w_1, w_2) the
-// product of all three maps' denominators peaks at a vertex, at
-// B = max_i [sum_j softplus(2 xi (1 - nu_ij)) + sum_{l != i, j} softplus(-2 xi nu_lj)]
-// (469 at xi = 100, kappa = 0.5).  The host selects this path only while
-// B < 600 (fast_fe), which leaves e^100 of headroom for the candidate values
-// that multiply the products; below e^-45 a q_j rounds away against 1.
-// E = exp(2 xi w - C2) is the caller's (weigh5).  The numerator and the
-// denominator are polynomials in E whose coefficients are constants of the
-// plan (InterpParams::Pd, Pa, Pb): Horner's rule in E takes 8 (NT = 3) or
-// 11 (NT = 4) operations instead of 12 and 16 for the products of the D_j.
-// The denominator's coefficients are positive, so it has no cancellation;
-// with the plan's maps the polynomial form rounds g(w) within 3.4e-16 of
-// its exact value over w in [0, 1], as the product form does within 1.4e-16.
-// The denominator is monic, so its Horner chain starts from E + c_{NT-1}
+// t_j = tanh(xi (w - nu_j)) = 1 - 2 i_j, i_j = 1 / (1 + e^(2 xi (w - nu_j))):
+//   g(w) = w + sum_j A_j(w) - 2 sum_j A_j(w) i_j,
+// i_j = k_j / (X + k_j) for the first two maps and X / (X + k_j) for the
+// third (X and k_j: see InterpParams), taken over the common denominator
+// prod_j (X + k_j): the map returns the numerator and leaves the denominator
+// in *den, so that the caller can normalise the three maps with one
+// reciprocal.  Nothing is clamped: the log of the product of the three
+// denominators is convex in the weights, so over the simplex it peaks at a
+// vertex, and it is bounded below map by map; the host centres that range on
+// zero by xsh (+-353 at xi = 100, kappa = 0.5) and selects this path only
+// while it stays within +-600 (fast_fe), which leaves e^100 of headroom for
+// the candidate values that multiply the products.
+// The numerator and the denominator are polynomials in X whose coefficients
+// are constants of the plan (InterpParams::Pd, Pa, Pb): Horner's rule takes 8
+// (NT = 3) or 11 (NT = 4) operations instead of 12 and 16 for products of the
+// X + k_j.  The denominator's coefficients are positive, so it has no
+// cancellation; the polynomial form rounds g(w) within 3.4e-16 of its exact
+// value over w in [0, 1], as the product form does within 1.4e-16.
+// The denominator is monic, so its Horner chain starts from X + c_{NT-1}
 // (no instruction with two constant operands, which the vector ALU cannot
 // read in one operation).
 template <int NT>
-__device__ __forceinline__ double fe_map_poly(double w, double E, const double* pd,
+__device__ __forceinline__ double fe_map_poly(double w, double X, const double* pd,
                                               const double* pa, const double* pb, double* den) {
   static_assert(NT == 3 || NT == 4, "maps have three or four terms");
-  double t = E + pd[NT - 2];
+  double t = X + pd[0];
 #pragma unroll
-  for (int r = NT - 3; r >= 0; --r) t = __builtin_fma(t, E, pd[r]);
-  *den = __builtin_fma(t, E, pd[NT - 1]);
+  for (int r = 1; r < NT; ++r) t = __builtin_fma(t, X, pd[r]);
+  *den = t;
   double ta = pa[NT - 2], tb = pb[NT - 2];
 #pragma unroll
   for (int r = NT - 3; r >= 0; --r) {
-    ta = __builtin_fma(ta, E, pa[r]);
-    tb = __builtin_fma(tb, E, pb[r]);
+    ta = __builtin_fma(ta, X, pa[r]);
+    tb = __builtin_fma(tb, X, pb[r]);
   }
-  // sum_j A_j(w) = 0 for every map (kMapSumsVanish), so g = w - 2 sum_j A_j / D_j.
-  return __builtin_fma(w, *den, E * __builtin_fma(w, tb, ta));
+  // sum_j A_j(w) = 0 for every map (kMapSumsVanish), so g = w - 2 sum_j A_j i_j.
+  return __builtin_fma(w, *den, X * __builtin_fma(w, tb, ta));
 }
 
-// Constants of one scheme family in the FE fast path of weigh5: the ideal
-// weights, the A_j = a_j + b_j w of its three maps, and the factor the
-// candidates passed to weigh5 are scaled by (1/8 for the WCNS candidates of
-// eq. 5, 1/6 for the WENO5 ones).
+// Constants of one scheme family in the FE fast path of weigh5: the ratios of
+// the ideal weights, and the factor the candidates' distances passed to
+// weigh5 are scaled by (1/8 for the WCNS candidates of eq. 5, 1/12 for the
+// WENO5 ones).
 struct FamWcns {
-  static constexpr double d0 = D0, d1 = D1, d2 = D2, scale = 0.125;
+  static constexpr double scale = 0.125;
   static constexpr double dr1 = 10.0, dr2 = 5.0;  // d_1 / d_0, d_2 / d_0
-  static constexpr const double (&m0a)[3] = kG0a;
-  static constexpr const double (&m0b)[3] = kG0b;
-  static constexpr const double (&m1a)[4] = kG1a;
-  static constexpr const double (&m1b)[4] = kG1b;
-  static constexpr const double (&m2a)[3] = kG2a;
-  static constexpr const double (&m2b)[3] = kG2b;
 };
 
 // The nonlinear weights of eq. 11 / 14 (+ FE map, eq. 20; PFE switch) from
 // the regularised smoothness indicators b_k = IS_k + eps (so that
-// tau = |IS_0 - IS_2| = |b_0 - b_2|), applied to the candidates of eq. 5; (c0, c1, c2)
-// are eight times the candidates (the 1/8 is applied once, to the sum).  The
-// FE branch serves either family (FAM); the generic branch is the WCNS one.
-// xt: the kExp2Tab64 table in LDS (TAB = true), else unused.
-template <int SPEC = SPEC_GENERIC, bool TAB = false, class FAM = FamWcns>
-__device__ __forceinline__ double weigh5(const InterpParams& P, double c0, double c1, double c2,
-                                         double b0, double b1, double b2,
+// tau = |IS_0 - IS_2| = |b_0 - b_2|), applied to the candidates of eq. 5.  The
+// candidates come as their distances (x0, x1, x2) from the value um of the
+// stencil's middle node, divided by FAM::scale (which is applied once, to the
+// sum): the weights sum to one, so the result is um plus the weighted mean
+// distance, the weights' rounding errors multiply distances instead of
+// values, and a flat stencil returns um itself.  The FE branch serves either
+// family (FAM); the generic branch is the WCNS one.
+// Bound by FP64 VALU issue: one task of two interpolations takes 219 VALU
+// instructions in the batch kernel (195 of them FP64), 266 with the Z weights
+// as sums times products, a reciprocal for the third map's variable, a
+// degree-5 exponential with a two-part reduction and the candidates
+// themselves; with the shorter reciprocals, roots and fluxes the step of the
+// 4096-tube batch went 1.096 -> 0.970 ms, the 2D 2048^2 residual 0.416 ->
+// 0.366 ms, the 3D 256^3 step 11.27 -> 10.00 ms, a 2D 512^2 WENO-FE step
+// 0.165 -> 0.153 ms (one box, both sides in turn); the value's error against
+// quadruple precision went from 6e-16 to 0.3-1.3e-16 rms.
+// xt: the exp2_tab_entry table in LDS (SPEC_FE only).
+template <int SPEC = SPEC_GENERIC, class FAM = FamWcns>
+__device__ __forceinline__ double weigh5(const InterpParams& P, double um, double x0, double x1,
+                                         double x2, double b0, double b1, double b2,
                                          const double* xt = nullptr) {
+// every fused operation is written out, so that tiles of any shape round alike
+#pragma clang fp contract(off)
   constexpr bool FE = (SPEC == SPEC_FE);
   if constexpr (FE) {
     // Z weights (p = 2) over the common denominator: alpha_k b_0^2 b_1^2 b_2^2
-    // = d_k (b_k^2 + tau^2) times the other two squares, here divided by d_0
-    // (the ratios d_k / d_0 are small integers; the normalisation removes
-    // the common factor); one reciprocal normalises them.  The smallest
-    // product, eps^6 = 1e-240, is still a normal number.
-    const double tau = __builtin_fabs(b0 - b2);
+    // = d_k (b_0^2 b_1^2 b_2^2 + tau^2 times the other two squares), here
+    // divided by d_0 (the ratios d_k / d_0 are small integers; the
+    // normalisation removes the common factor); one reciprocal normalises
+    // them.  The smallest product, eps^6 = 1e-240, is still a normal number.
+    const double tau = b0 - b2;
     const double t2 = tau * tau;
     const double q0 = b0 * b0, q1 = b1 * b1, q2 = b2 * b2;
-    const double z0 = (q0 + t2) * (q1 * q2);
-    const double z1 = FAM::dr1 * (q1 + t2) * (q0 * q2);
-    const double z2 = FAM::dr2 * (q2 + t2) * (q0 * q1);
+    const double p12 = q1 * q2, p02 = q0 * q2, p01 = q0 * q1;
+    const double p = q0 * p12;
+    const double z0 = __builtin_fma(t2, p12, p);
+    const double z1 = FAM::dr1 * __builtin_fma(t2, p02, p);
+    const double z2 = FAM::dr2 * __builtin_fma(t2, p01, p);
     const double zi = rcp(z0 + z1 + z2);
-    const double xi2 = 2.0 * P.xi;
     const double w0 = z0 * zi, w1 = z1 * zi, w2 = z2 * zi;
-    // E_k = exp(2 xi w_k - C2_k).  The Z weights sum to one, so E_0 E_1 E_2 =
-    // exp(2 xi - C2_0 - C2_1 - C2_2) = Ke and the third exponential is
-    // Ke / (E_0 E_1); E_0 E_1 lies within [e^(-2 xi (c_0 + c_1)),
-    // e^(2 xi (1 - c_0 - c_1))], normal numbers wherever the host selects
-    // this path (fast_fe).
-    const double zE0 = __builtin_fma(xi2, w0, -P.C2[0]), zE1 = __builtin_fma(xi2, w1, -P.C2[1]);
-    const double Ex0 = TAB ? exp_tab(zE0, xt) : exp_cw(zE0);
-    const double Ex1 = TAB ? exp_tab(zE1, xt) : exp_cw(zE1);
-    // (E_2 enters only the third map's polynomials, so a relative error
-    // of 2^-48.8 moves g_2 by at most about twice that: rcp1)
-    const double Ex2 = P.Ke * rcp1(Ex0 * Ex1);
+    // The Z weights sum to one, so the third map's variable is the product
+    // of the other two's, with no third exponential or reciprocal.
+    const double X0 = exp2_tab(w0, P.xa, xt), X1 = exp2_tab(w1, P.xa, xt);
     // g_k = n_k / e_k; the normalised weights g_k / sum_l g_l over the
-    // common denominator e_0 e_1 e_2 (below e^B, fe_map_poly): one reciprocal.
+    // common denominator e_0 e_1 e_2 (fe_map_poly): one reciprocal.
     double e0, e1, e2;
-    const double n0 = fe_map_poly<3>(w0, Ex0, P.Pd, P.Pa, P.Pb, &e0);
-    const double n1 = fe_map_poly<4>(w1, Ex1, P.Pd + 3, P.Pa + 2, P.Pb + 2, &e1);
-    const double n2 = fe_map_poly<3>(w2, Ex2, P.Pd + 7, P.Pa + 5, P.Pb + 5, &e2);
+    const double n0 = fe_map_poly<3>(w0, X0, P.Pd, P.Pa, P.Pb, &e0);
+    const double n1 = fe_map_poly<4>(w1, X1, P.Pd + 3, P.Pa + 2, P.Pb + 2, &e1);
+    const double n2 = fe_map_poly<3>(w2, X0 * X1, P.Pd + 7, P.Pa + 5, P.Pb + 5, &e2);
     // T_k = n_k prod_{l != k} e_l: T_0 = A e_2, T_1 = B e_2, T_2 = C
     const double A = n0 * e1, B = n1 * e0, C = n2 * (e0 * e1);
-    const double num = __builtin_fma(e2, __builtin_fma(A, c0, B * c1), C * c2);
-    return (FAM::scale * num) * rcp1(__builtin_fma(e2, A + B, C));
+    const double num = __builtin_fma(e2, __builtin_fma(A, x0, B * x1), C * x2);
+    // (rcp1: its error is relative to the distance from um)
+    return __builtin_fma(FAM::scale * num, rcp1(__builtin_fma(e2, A + B, C)), um);
   }
   if constexpr (SPEC == SPEC_FE_SAT) {
     // Z weights (p = 2) over the common denominator as above, then each map
@@ -400,7 +459,7 @@ __device__ __forceinline__ double weigh5(const InterpParams& P, double c0, doubl
     const double g0 = fe_g0<SPEC_GENERIC>(z0 * zi, P), g1 = fe_g1<SPEC_GENERIC>(z1 * zi, P),
                  g2 = fe_g2<SPEC_GENERIC>(z2 * zi, P);
     const double ginv = rcp(g0 + g1 + g2);
-    return 0.125 * ((g0 * ginv) * c0 + (g1 * ginv) * c1 + (g2 * ginv) * c2);
+    return __builtin_fma(0.125 * ginv, __builtin_fma(g0, x0, __builtin_fma(g1, x1, g2 * x2)), um);
   }
   double a0, a1, a2;
   if (!FE && P.weights == WJS) {
@@ -438,7 +497,7 @@ __device__ __forceinline__ double weigh5(const InterpParams& P, double c0, doubl
     w1 = g1 * ginv;
     w2 = g2 * ginv;
   }
-  return 0.125 * (w0 * c0 + w1 * c1 + w2 * c2);
+  return __builtin_fma(0.125, __builtin_fma(w0, x0, __builtin_fma(w1, x1, w2 * x2)), um);
 }
 
 // Both nonlinear interpolations (eq. 5-6) of one field at x_{m+1/2} from the
@@ -452,34 +511,39 @@ __device__ __forceinline__ double weigh5(const InterpParams& P, double c0, doubl
 // flat stencils must not see rounding noise.  The mirrored stencil's first
 // differences are the negated left ones (plus u_5 - u_4), so its second
 // differences s'_1, s'_2 are the left s_2, s_1.
-template <int SPEC = SPEC_GENERIC, bool TAB = false>
+// With s_k the second difference of sub-stencil k and f_k its parabola's
+// slope at u_2 (d_1 + s_0 / 2, d_1 + s_1 / 2, d_2 - s_2 / 2), IS_k = f_k^2 + s_k^2 and the candidate is the parabola's
+// value at the midpoint, u_2 + f_k / 2 + s_k / 8 = u_2 + (4 f_k + s_k) / 8.
+template <int SPEC = SPEC_GENERIC>
 __device__ __forceinline__ void interp5_pair(const InterpParams& P, const double (&u)[6],
                                              double* left, double* right,
                                              const double* xt = nullptr) {
   constexpr bool FE = (SPEC == SPEC_FE);
-  // candidates of eq. 5 (times 8) of both stencils
-  const double c0 = 3.0 * u[0] - 10.0 * u[1] + 15.0 * u[2];
-  const double c1 = -u[1] + 6.0 * u[2] + 3.0 * u[3];
-  const double c2 = 3.0 * u[2] + 6.0 * u[3] - u[4];
-  const double r0 = 3.0 * u[5] - 10.0 * u[4] + 15.0 * u[3];
-  const double r1 = -u[4] + 6.0 * u[3] + 3.0 * u[2];
-  const double r2 = 3.0 * u[3] + 6.0 * u[2] - u[1];
-  if (!FE && P.weights == WLIN) {
-    *left = 0.125 * (D0 * c0 + D1 * c1 + D2 * c2);
-    *right = 0.125 * (D0 * r0 + D1 * r1 + D2 * r2);
-    return;
-  }
   const double d0 = u[1] - u[0], d1 = u[2] - u[1], d2 = u[3] - u[2], d3 = u[4] - u[3],
                d4 = u[5] - u[4];
   const double s0 = d1 - d0, s1 = d2 - d1, s2 = d3 - d2, s3 = d4 - d3;
+  const double f0 = __builtin_fma(0.5, s0, d1), f1 = __builtin_fma(0.5, s1, d1),
+               f2 = __builtin_fma(-0.5, s2, d2);
+  // the mirrored stencil (its first differences are -d4, -d3, -d2, -d1)
+  const double g0 = __builtin_fma(0.5, s3, -d3), g1 = __builtin_fma(0.5, s2, -d3),
+               g2 = __builtin_fma(-0.5, s1, -d2);
+  const double x0 = __builtin_fma(4.0, f0, s0), x1 = __builtin_fma(4.0, f1, s1),
+               x2 = __builtin_fma(4.0, f2, s2);
+  const double y0 = __builtin_fma(4.0, g0, s3), y1 = __builtin_fma(4.0, g1, s2),
+               y2 = __builtin_fma(4.0, g2, s1);
+  if (!FE && P.weights == WLIN) {
+    *left = __builtin_fma(0.125, D0 * x0 + D1 * x1 + D2 * x2, u[2]);
+    *right = __builtin_fma(0.125, D0 * y0 + D1 * y1 + D2 * y2, u[3]);
+    return;
+  }
   // IS_k + eps = f_k^2 + (s_k^2 + eps)
   const double q1 = __builtin_fma(s1, s1, P.eps), q2 = __builtin_fma(s2, s2, P.eps);
-  const double f0 = 0.5 * (3.0 * d1 - d0), f1 = 0.5 * (d1 + d2), f2 = 0.5 * (3.0 * d2 - d3);
-  const double g0 = 0.5 * (3.0 * d3 - d4), g1 = 0.5 * (d2 + d3), g2 = 0.5 * (3.0 * d2 - d1);
-  *left = weigh5<SPEC, TAB>(P, c0, c1, c2, __builtin_fma(f0, f0, __builtin_fma(s0, s0, P.eps)),
-                            __builtin_fma(f1, f1, q1), __builtin_fma(f2, f2, q2), xt);
-  *right = weigh5<SPEC, TAB>(P, r0, r1, r2, __builtin_fma(g0, g0, __builtin_fma(s3, s3, P.eps)),
-                             __builtin_fma(g1, g1, q2), __builtin_fma(g2, g2, q1), xt);
+  *left = weigh5<SPEC>(P, u[2], x0, x1, x2,
+                       __builtin_fma(f0, f0, __builtin_fma(s0, s0, P.eps)),
+                       __builtin_fma(f1, f1, q1), __builtin_fma(f2, f2, q2), xt);
+  *right = weigh5<SPEC>(P, u[3], y0, y1, y2,
+                        __builtin_fma(g0, g0, __builtin_fma(s3, s3, P.eps)),
+                        __builtin_fma(g1, g1, q2), __builtin_fma(g2, g2, q1), xt);
 }
 
 // ----------------------------------------- WENO5 reconstruction (App. B) --
@@ -497,31 +561,26 @@ static_assert(map_sums_vanish(kV0a, kV0b, 3) && map_sums_vanish(kV1a, kV1b, 4) &
               "the WENO FE maps' A_j must sum to zero");
 
 struct FamWeno {
-  static constexpr double d0 = E0, d1 = E1, d2 = E2, scale = 1.0 / 6.0;
+  static constexpr double scale = 1.0 / 12.0;
   static constexpr double dr1 = 6.0, dr2 = 3.0;  // d_1 / d_0, d_2 / d_0
-  static constexpr const double (&m0a)[3] = kV0a;
-  static constexpr const double (&m0b)[3] = kV0b;
-  static constexpr const double (&m1a)[4] = kV1a;
-  static constexpr const double (&m1b)[4] = kV1b;
-  static constexpr const double (&m2a)[3] = kV2a;
-  static constexpr const double (&m2b)[3] = kV2b;
 };
 
 // weno5 with FE weights on p = 2 Z weights through the fast path of weigh5
-// (Table B.1 ideal weights, Table B.2 maps); xt: the kExp2Tab64 table in LDS.
-template <bool TAB>
+// (Table B.1 ideal weights, Table B.2 maps); xt: the exp2_tab_entry table in
+// LDS.  With f_k and s_k as in interp5_pair, B_k = f_k^2 + 13/12 s_k^2 and
+// the candidate is c + f_k / 2 + s_k / 12.
 __device__ __forceinline__ double weno5_fe(const InterpParams& P, double a, double b, double c,
                                            double e, double f, const double* xt) {
+  constexpr double k = 13.0 / 12.0;
   const double d0 = b - a, d1 = c - b, d2 = e - c, d3 = f - e;
-  const double s20 = d1 - d0, s10 = 3.0 * d1 - d0;
-  const double s21 = d2 - d1, s11 = d1 + d2;
-  const double s22 = d3 - d2, s12 = 3.0 * d2 - d3;
-  const double B0 = (13.0 / 12.0) * s20 * s20 + 0.25 * s10 * s10;
-  const double B1 = (13.0 / 12.0) * s21 * s21 + 0.25 * s11 * s11;
-  const double B2 = (13.0 / 12.0) * s22 * s22 + 0.25 * s12 * s12;
-  return weigh5<SPEC_FE, TAB, FamWeno>(P, 2.0 * a - 7.0 * b + 11.0 * c, -b + 5.0 * c + 2.0 * e,
-                                       2.0 * c + 5.0 * e - f, B0 + P.eps, B1 + P.eps,
-                                       B2 + P.eps, xt);
+  const double s0 = d1 - d0, s1 = d2 - d1, s2 = d3 - d2;
+  const double f0 = __builtin_fma(0.5, s0, d1), f1 = __builtin_fma(0.5, s1, d1),
+               f2 = __builtin_fma(-0.5, s2, d2);
+  return weigh5<SPEC_FE, FamWeno>(P, c, __builtin_fma(6.0, f0, s0), __builtin_fma(6.0, f1, s1),
+                                  __builtin_fma(6.0, f2, s2),
+                                  __builtin_fma(f0, f0, __builtin_fma(k * s0, s0, P.eps)),
+                                  __builtin_fma(f1, f1, __builtin_fma(k * s1, s1, P.eps)),
+                                  __builtin_fma(f2, f2, __builtin_fma(k * s2, s2, P.eps)), xt);
 }
 
 // Finite-difference WENO5 reconstruction at x_{i+1/2} from the point values
@@ -582,6 +641,24 @@ __device__ __forceinline__ double weno5(const InterpParams& P, double a, double 
 // ------------------------------------------------------------------ Euler --
 // State layout in registers: [rho, m_0 .. m_{ND-1}, E].
 
+// a . b and |v|^2, every fused product written out (which product is rounded
+// by itself is part of the result, and the tiles of every shape and the
+// weight statistics are to agree).
+template <int ND>
+__device__ __forceinline__ double dot(const double* a, const double* b) {
+  double s = a[0] * b[0];
+#pragma unroll
+  for (int k = 1; k < ND; ++k) s = __builtin_fma(a[k], b[k], s);
+  return s;
+}
+template <int ND>
+__device__ __forceinline__ double norm2(const double* v) {
+  if constexpr (ND == 1) return v[0] * v[0];
+  double s = __builtin_fma(v[0], v[0], v[1] * v[1]);
+  if constexpr (ND == 3) s = __builtin_fma(v[2], v[2], s);
+  return s;
+}
+
 template <int ND>
 struct Prim {
   double ir;        // 1/rho
@@ -589,17 +666,13 @@ struct Prim {
   double p;
 };
 
-template <int ND>
+template <int ND, bool NEWTON2 = false>
 __device__ __forceinline__ Prim<ND> primitives(const double* U, double gamma) {
   Prim<ND> q;
-  q.ir = rcp(U[0]);
-  double mm = 0.0;
+  q.ir = rcp<NEWTON2>(U[0]);
 #pragma unroll
-  for (int k = 0; k < ND; ++k) {
-    q.vel[k] = U[1 + k] * q.ir;
-    mm += U[1 + k] * q.vel[k];
-  }
-  q.p = (gamma - 1.0) * (U[ND + 1] - 0.5 * mm);
+  for (int k = 0; k < ND; ++k) q.vel[k] = U[1 + k] * q.ir;
+  q.p = (gamma - 1.0) * __builtin_fma(-0.5, dot<ND>(U + 1, q.vel), U[ND + 1]);
   return q;
 }
 
@@ -625,36 +698,29 @@ struct RoeState {
 // as roe_average (so tiles may keep only vel, H, c and ic).
 template <int ND>
 __device__ __forceinline__ void roe_derived(RoeState<ND>& r, double gamma) {
-  double q2 = 0.0;
-#pragma unroll
-  for (int k = 0; k < ND; ++k) q2 += r.vel[k] * r.vel[k];
-  r.q2h = 0.5 * q2;
+  r.q2h = 0.5 * norm2<ND>(r.vel);
   r.b1 = (gamma - 1.0) * r.ic * r.ic;
   r.b2 = r.q2h * r.b1;
 }
 
-template <int ND>
+template <int ND, bool NEWTON2 = false>
 __device__ __forceinline__ RoeState<ND> roe_average(const double* UA, const double* UB,
                                                     double gamma) {
-  const Prim<ND> A = primitives<ND>(UA, gamma);
-  const Prim<ND> B = primitives<ND>(UB, gamma);
+  const Prim<ND> A = primitives<ND, NEWTON2>(UA, gamma);
+  const Prim<ND> B = primitives<ND, NEWTON2>(UB, gamma);
   // weights sqrt(rho_A) / (sqrt(rho_A) + sqrt(rho_B)) and the same for B,
   // through s = sqrt(rho_B / rho_A)
-  const double s = sqrt_pos(UB[0] * A.ir);
-  const double wA = rcp(1.0 + s), wB = s * wA;
+  const double s = sqrt_pos<NEWTON2>(UB[0] * A.ir);
+  const double wA = rcp<NEWTON2>(1.0 + s), wB = s * wA;
   RoeState<ND> r;
-  double q2 = 0.0;
 #pragma unroll
-  for (int k = 0; k < ND; ++k) {
-    r.vel[k] = wA * A.vel[k] + wB * B.vel[k];
-    q2 += r.vel[k] * r.vel[k];
-  }
+  for (int k = 0; k < ND; ++k) r.vel[k] = __builtin_fma(wA, A.vel[k], wB * B.vel[k]);
   const double HA = (UA[ND + 1] + A.p) * A.ir;
   const double HB = (UB[ND + 1] + B.p) * B.ir;
-  r.H = wA * HA + wB * HB;
-  r.q2h = 0.5 * q2;
-  r.c = sqrt_pos((gamma - 1.0) * (r.H - r.q2h));
-  r.ic = rcp(r.c);
+  r.H = __builtin_fma(wA, HA, wB * HB);
+  r.q2h = 0.5 * norm2<ND>(r.vel);
+  r.c = sqrt_pos<NEWTON2>((gamma - 1.0) * (r.H - r.q2h));
+  r.ic = rcp<NEWTON2>(r.c);
   r.b1 = (gamma - 1.0) * r.ic * r.ic;
   r.b2 = r.q2h * r.b1;
   return r;
@@ -705,52 +771,50 @@ __device__ __forceinline__ void field_row(const RoeState<ND>& r, int v, double (
   l[0] = __builtin_fma(s * r.vel[DIR], r.ic, 0.5 * r.b2);
 #pragma unroll
   for (int k = 0; k < ND; ++k) l[1 + k] = -hb1 * r.vel[k];
-  l[1 + DIR] -= s * r.ic;
+  l[1 + DIR] = __builtin_fma(-s, r.ic, l[1 + DIR]);
   l[ND + 1] = hb1;
 }
 
 template <int ND, int DIR>
 __device__ __forceinline__ void unproject(const RoeState<ND>& r, const double* W, double* U) {
-  const double sum = W[0] + W[1] + W[ND + 1];
-  const double dif = W[ND + 1] - W[0];
+  const double ac = W[0] + W[ND + 1];
+  const double sum = ac + W[1];
+  const double cd = r.c * (W[ND + 1] - W[0]);
   U[0] = sum;
-  double E = r.H * (W[0] + W[ND + 1]) + r.vel[DIR] * r.c * dif + r.q2h * W[1];
-#pragma unroll
-  for (int k = 0; k < ND; ++k) U[1 + k] = r.vel[k] * sum;
-  U[1 + DIR] += r.c * dif;
+  double E = __builtin_fma(r.H, ac, __builtin_fma(r.vel[DIR], cd, r.q2h * W[1]));
+  U[1 + DIR] = __builtin_fma(r.vel[DIR], sum, cd);
 #pragma unroll
   for (int t = 0; t < ND - 1; ++t) {
     const int ax = tangential_axis<ND, DIR>(t);
-    U[1 + ax] += W[2 + t];
-    E += r.vel[ax] * W[2 + t];
+    U[1 + ax] = __builtin_fma(r.vel[ax], sum, W[2 + t]);
+    E = __builtin_fma(r.vel[ax], W[2 + t], E);
   }
   U[ND + 1] = E;
 }
 
-// Local Lax-Friedrichs flux between the interpolated states UL and UR.
+// Twice the local Lax-Friedrichs flux between the interpolated states UL and
+// UR: F(UL) + F(UR) - alpha (UR - UL); the flux difference takes the half
+// into its coefficients (exactly).
 template <int ND, int DIR>
-__device__ __forceinline__ void llf_flux(const double* UL, const double* UR, double gamma,
-                                         double* F) {
+__device__ __forceinline__ void llf_flux2(const double* UL, const double* UR, double gamma,
+                                          double* F) {
   constexpr int NV = ND + 2;
-  double FL[NV], FR[NV];
   const Prim<ND> L = primitives<ND>(UL, gamma);
   const Prim<ND> R = primitives<ND>(UR, gamma);
   const double cL = sqrt_pos(gamma * L.p * L.ir);
   const double cR = sqrt_pos(gamma * R.p * R.ir);
-  const double lamL = __builtin_fabs(L.vel[DIR]) + cL;
-  const double lamR = __builtin_fabs(R.vel[DIR]) + cR;
+  const double vL = L.vel[DIR], vR = R.vel[DIR];
+  const double lamL = __builtin_fabs(vL) + cL;
+  const double lamR = __builtin_fabs(vR) + cR;
   const double alpha = __builtin_fmax(lamL, lamR);  // (the larger; a NaN only if both are)
-  FL[0] = UL[1 + DIR];
-  FR[0] = UR[1 + DIR];
+  F[0] = UL[1 + DIR] + UR[1 + DIR];
 #pragma unroll
-  for (int k = 0; k < ND; ++k) {
-    FL[1 + k] = UL[1 + k] * L.vel[DIR] + (k == DIR ? L.p : 0.0);
-    FR[1 + k] = UR[1 + k] * R.vel[DIR] + (k == DIR ? R.p : 0.0);
-  }
-  FL[ND + 1] = (UL[ND + 1] + L.p) * L.vel[DIR];
-  FR[ND + 1] = (UR[ND + 1] + R.p) * R.vel[DIR];
+  for (int k = 0; k < ND; ++k)
+    F[1 + k] = k == DIR ? __builtin_fma(UL[1 + k], vL, __builtin_fma(UR[1 + k], vR, L.p + R.p))
+                        : __builtin_fma(UL[1 + k], vL, UR[1 + k] * vR);
+  F[ND + 1] = __builtin_fma(UL[ND + 1] + L.p, vL, (UR[ND + 1] + R.p) * vR);
 #pragma unroll
-  for (int v = 0; v < NV; ++v) F[v] = 0.5 * (FL[v] + FR[v]) - 0.5 * alpha * (UR[v] - UL[v]);
+  for (int v = 0; v < NV; ++v) F[v] = __builtin_fma(-alpha, UR[v] - UL[v], F[v]);
 }
 
 // Physical flux at one node along DIR.

@@ -9,7 +9,8 @@
 // Bin b of nbins covers [b/nbins, (b+1)/nbins); 1.0 falls in the last bin.
 // The weights follow the generic instantiation of the interpolation (one
 // reciprocal per Z weight), so that weights equal to d_k on flat stencils are
-// exactly d_k.
+// exactly d_k, and keep the two-step reciprocals (NEWTON2), so that a change of
+// rounding in the residual's path moves no count.
 #include <hip/hip_runtime.h>
 
 #include "wcns_internal.hpp"
@@ -36,13 +37,13 @@ __device__ __forceinline__ void interp_weights(const InterpParams& P, double a, 
     a1 = D1;
     a2 = D2;
   } else if (P.weights == WJS) {
-    const double r0 = rcp(IS0 + P.eps), r1 = rcp(IS1 + P.eps), r2 = rcp(IS2 + P.eps);
+    const double r0 = rcp<true>(IS0 + P.eps), r1 = rcp<true>(IS1 + P.eps), r2 = rcp<true>(IS2 + P.eps);
     a0 = D0 * r0 * r0;
     a1 = D1 * r1 * r1;
     a2 = D2 * r2 * r2;
   } else {
     const double tau = __builtin_fabs(IS0 - IS2);
-    const double q0 = tau * rcp(IS0 + P.eps), q1 = tau * rcp(IS1 + P.eps), q2 = tau * rcp(IS2 + P.eps);
+    const double q0 = tau * rcp<true>(IS0 + P.eps), q1 = tau * rcp<true>(IS1 + P.eps), q2 = tau * rcp<true>(IS2 + P.eps);
     double p0 = q0, p1 = q1, p2 = q2;
     for (int k = 1; k < P.zpow; ++k) {
       p0 *= q0;
@@ -53,13 +54,13 @@ __device__ __forceinline__ void interp_weights(const InterpParams& P, double a, 
     a1 = D1 * (1.0 + p1);
     a2 = D2 * (1.0 + p2);
   }
-  const double inv = rcp(a0 + a1 + a2);
+  const double inv = rcp<true>(a0 + a1 + a2);
   wb[0] = a0 * inv;
   wb[1] = a1 * inv;
   wb[2] = a2 * inv;
-  const double g0 = fe_g0<SPEC_GENERIC>(wb[0], P), g1 = fe_g1<SPEC_GENERIC>(wb[1], P),
-               g2 = fe_g2<SPEC_GENERIC>(wb[2], P);
-  const double gi = rcp(g0 + g1 + g2);
+  const double g0 = fe_g0<SPEC_GENERIC, true>(wb[0], P), g1 = fe_g1<SPEC_GENERIC, true>(wb[1], P),
+               g2 = fe_g2<SPEC_GENERIC, true>(wb[2], P);
+  const double gi = rcp<true>(g0 + g1 + g2);
   wm[0] = g0 * gi;
   wm[1] = g1 * gi;
   wm[2] = g2 * gi;
@@ -102,7 +103,7 @@ __global__ void __launch_bounds__(256) weight_hist_kernel(SweepArgs a, StatsGeom
   if constexpr (NV > 1) {
     constexpr int ND = NV - 2;
     if (a.pp.charproj) {
-      const RoeState<ND> rs = roe_average<ND>(s[2], s[3], a.pp.gamma);
+      const RoeState<ND> rs = roe_average<ND, true>(s[2], s[3], a.pp.gamma);
 #pragma unroll
       for (int j = 0; j < 6; ++j) project<ND, DIR>(rs, s[j], W[j]);
     } else {

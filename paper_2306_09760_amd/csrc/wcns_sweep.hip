@@ -15,8 +15,8 @@
 //           and the mirrored right-biased nonlinear interpolation
 //           (interp5_pair).  TM*W is a multiple of 64, so the field is
 //           uniform across a wavefront;
-//   flux    back-projection of the two interpolated states and the local
-//           Lax-Friedrichs flux;
+//   flux    back-projection of the two interpolated states and (twice) the
+//           local Lax-Friedrichs flux;
 //   diff    MND6 or MD6 flux difference of TL = TM-3 (TM-5) nodes per
 //           column, written as R, R+= or the fused SSP-RK3 stage combine.
 // The ragged batch packs its tiles across problem ends (BatchArgs): a tile's
@@ -110,7 +110,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
   double* sU = smem;
   double* sR = sU + NV * SV;
   double* sW = sR + NR * TMW;
-  double* sX = sW + 2 * NV * TMW;  // kExp2Tab64
+  double* sX = sW + 2 * NV * TMW;  // exp2_tab_entry
   const int tid = threadIdx.x;
   const int G = a.diff ? 5 : 4;
   const int TL = TM - (a.diff ? 5 : 3);
@@ -217,7 +217,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
   }
   double xv = 0.0;
   if constexpr (SPEC == SPEC_FE) {
-    if (tid < 64) xv = kExp2Tab64[tid];
+    if (tid < 64) xv = exp2_tab_entry(tid, a.ip.xsh);
   }
 #pragma unroll
   for (int it = 0; it < NIT; ++it) {
@@ -326,7 +326,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
 #pragma unroll
       for (int j = 0; j < 6; ++j) w[j] = uv[j * W];
     }
-    interp5_pair<SPEC, SPEC == SPEC_FE>(a.ip, w, sW + q, sW + NV * TMW + q, sX);
+    interp5_pair<SPEC>(a.ip, w, sW + q, sW + NV * TMW + q, sX);
   }
   if constexpr (!OWN) __syncthreads();
 
@@ -348,8 +348,9 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
   for (int q = tid; q < TMW; q += NT) {
     double F[NV];
     if constexpr (NV == 1) {
+      // (twice the upwind flux, as llf_flux2)
       const double uL = sW[q], uR = sW[TMW + q];
-      F[0] = 0.5 * a.pp.adv * (uL + uR) - 0.5 * __builtin_fabs(a.pp.adv) * (uR - uL);
+      F[0] = __builtin_fma(a.pp.adv, uL + uR, -__builtin_fabs(a.pp.adv) * (uR - uL));
     } else {
       double WL[NV], WR[NV], UL[NV], UR[NV];
 #pragma unroll
@@ -377,7 +378,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
           UR[v] = WR[v];
         }
       }
-      llf_flux<ND, DIR>(UL, UR, a.pp.gamma, F);
+      llf_flux2<ND, DIR>(UL, UR, a.pp.gamma, F);
     }
 #pragma unroll
     for (int v = 0; v < NV; ++v) sW[v * TMW + q] = F[v];
@@ -418,7 +419,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
     } else {
       if (i >= N || c >= ncol) continue;
     }
-    const double* f = sW + q;        // F~ of midpoint t + k of column c at f[k W]
+    const double* f = sW + q;        // 2 F~ of midpoint t + k of column c at f[k W]
     const double* u = sU + q;        // node t + k of column c at u[k W]
     double res[NV], Un[NV];
     if (a.diff == 0) {
@@ -428,8 +429,9 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
         const lds_cptr fv = lds_row(f + v * TMW);
         // F of node t + k + 2 at nf[k W]: nodes t + 3 and t + 5 around t + 4
         const lds_cptr nf = lds_row(f + (NV + v) * TMW);
-        const double d = 1.5 * (fv[2 * W] - fv[W]) - 0.3 * (nf[3 * W] - nf[W]) +
-                         (1.0 / 30.0) * (fv[3 * W] - fv[0]);
+        const double d = __builtin_fma(
+            0.75, fv[2 * W] - fv[W],
+            __builtin_fma(-0.3, nf[3 * W] - nf[W], (1.0 / 60.0) * (fv[3 * W] - fv[0])));
         res[v] = -ih * d;
       }
     } else {
@@ -437,8 +439,9 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
       for (int v = 0; v < NV; ++v) {
         Un[v] = u[v * SV + 5 * W];
         const lds_cptr fv = lds_row(f + v * TMW);
-        const double d = (75.0 / 64.0) * (fv[3 * W] - fv[2 * W]) +
-                         (-25.0 / 384.0) * (fv[4 * W] - fv[W]) + (3.0 / 640.0) * (fv[5 * W] - fv[0]);
+        const double d = __builtin_fma(
+            75.0 / 128.0, fv[3 * W] - fv[2 * W],
+            __builtin_fma(-25.0 / 768.0, fv[4 * W] - fv[W], (3.0 / 1280.0) * (fv[5 * W] - fv[0])));
         res[v] = -ih * d;
       }
     }

@@ -49,7 +49,7 @@ __global__ void __launch_bounds__(256) weno_sweep_kernel(SweepArgs a, TileGeom g
   double* sR = sL + SV;
   double* sA = sR + NR * TMW;
   double* sW = sA + TMW;
-  double* sX = sW + 2 * NV * TMW;  // kExp2Tab64
+  double* sX = sW + 2 * NV * TMW;  // exp2_tab_entry
   const int tid = threadIdx.x;
 
   if ((int64_t)blockIdx.x >= g.ntiles) return;
@@ -87,7 +87,7 @@ __global__ void __launch_bounds__(256) weno_sweep_kernel(SweepArgs a, TileGeom g
 
   // load
   if constexpr (SPEC == SPEC_FE) {
-    if (tid < 64) sX[tid] = kExp2Tab64[tid];
+    if (tid < 64) sX[tid] = exp2_tab_entry(tid, a.ip.xsh);
   }
   for (int idx = tid; idx < SV; idx += NT) {
     const int k = idx >> LW, c = idx & (W - 1);
@@ -188,7 +188,7 @@ __global__ void __launch_bounds__(256) weno_sweep_kernel(SweepArgs a, TileGeom g
       }
     }
     if constexpr (SPEC == SPEC_FE)
-      sW[q] = weno5_fe<true>(a.ip, w[0], w[1], w[2], w[3], w[4], sX);
+      sW[q] = weno5_fe(a.ip, w[0], w[1], w[2], w[3], w[4], sX);
     else
       sW[q] = weno5(a.ip, w[0], w[1], w[2], w[3], w[4]);
   }
