@@ -155,9 +155,9 @@ void interp_params(const wcns_desc* d, InterpParams* ip) {
         b += softplus(2.0 * d->xi * ((m == i ? 1.0 : 0.0) - nu[first[m] + j]));
     B = std::max(B, b);
   }
-  // The adjoint takes the third map's exponential as Ke / (E_0 E_1): E_0 E_1
-  // = exp(2 xi (w_0 + w_1 - c_0 - c_1)) must stay a normal number for
-  // w_0 + w_1 in [0, 1].
+  // (The line of the path's earlier form, which took the third variable as a
+  // quotient of exponentials that had to stay normal; implied by B < 600 at
+  // the default kappa.)
   const bool prod_ok = 2.0 * d->xi < 650.0 && 2.0 * d->xi * (c[0] + c[1]) < 650.0 &&
                        std::fabs(2.0 * d->xi * (1.0 - c[0] - c[1] - c[2])) < 650.0;
   for (int m = 0; m < 3; ++m) {
@@ -167,13 +167,13 @@ void interp_params(const wcns_desc* d, InterpParams* ip) {
       ip->K[k] = ip->shared_exp ? std::exp(2.0 * d->xi * (c[m] - nu[k])) : nu[k];
     }
   }
-  ip->Ke = ip->shared_exp ? std::exp(2.0 * d->xi - ip->C2[0] - ip->C2[1] - ip->C2[2]) : 0.0;
   ip->fast_fe = (ip->shared_exp && B < 600.0 && prod_ok) ? 1 : 0;
   ip->xa = 0.0;
   ip->xsh = 0;
   std::fill(ip->Pd, ip->Pd + 10, 0.0);
   std::fill(ip->Pa, ip->Pa + 7, 0.0);
   std::fill(ip->Pb, ip->Pb + 7, 0.0);
+  std::fill(ip->kap, ip->kap + 10, 0.0);
   if (!ip->fast_fe) return;
   // The maps' variables and polynomials (InterpParams, fe_map_poly), in long
   // double with the steepness that the rounded xa stands for.
@@ -225,6 +225,7 @@ void interp_params(const wcns_desc* d, InterpParams* ip) {
       const long double n = nu[first[m] + j];
       k[j] = m < 2 ? std::exp(x2 * n - shift * ln2) : std::exp(x2 * (1.0L - n) - 2.0L * shift * ln2);
     }
+    for (int j = 0; j < nt; ++j) ip->kap[first[m] + j] = (double)k[j];
     esym(k, nt, e);
     for (int r = 1; r <= nt; ++r) ip->Pd[offd[m] + r - 1] = (double)e[r];
     for (int j = 0; j < nt; ++j) {

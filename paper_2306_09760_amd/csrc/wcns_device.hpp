@@ -54,7 +54,6 @@ struct InterpParams {
   //   shared_exp = 0:  K[j] = nu_j                      (C2 unused)
   double K[10];
   double C2[3];
-  double Ke;        // exp(2 xi - C2[0] - C2[1] - C2[2]) (shared_exp; the adjoint)
   // fe_map_poly (fast_fe).  X_0 = 2^-xsh e^(2 xi w_0), X_1 = 2^-xsh e^(2 xi
   // w_1) and X_2 = X_0 X_1 = 2^-2xsh e^(2 xi (1 - w_2)) are the variables of
   // the three maps; term j of map m is saturated to one side or the other as
@@ -66,6 +65,7 @@ struct InterpParams {
   //     (the coefficients of X^0 vanish);
   // maps at offsets 0, 3, 7 of Pd and 0, 2, 5 of Pa and Pb
   double Pd[10], Pa[7], Pb[7];
+  double kap[10];   // the k_j (the adjoint)
   double xa;        // 2 xi 64 / ln 2 (exp2_tab)
   int xsh;          // the shift of X_0 and X_1 (fast_fe)
   int weights;      // WJS .. WLIN
