@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <map>
 #include <mutex>
 #include <string>
@@ -124,6 +125,7 @@ void interp_params(const wcns_desc* d, InterpParams* ip) {
   ip->eps = d->eps;
   ip->xi = d->xi;
   ip->cv = d->cv;
+  ip->band = 20.0 / d->xi;
   double nu[10];
   fill_null_points(d->kappa, d->scheme, nu);
   ip->weno = d->scheme == WCNS_SCHEME_WENO ? 1 : 0;
@@ -143,6 +145,10 @@ void interp_params(const wcns_desc* d, InterpParams* ip) {
     for (int j = 0; j < count[m]; ++j) spread = std::max(spread, std::fabs(c[m] - nu[first[m] + j]));
   }
   ip->shared_exp = (d->xi * spread < 300.0) ? 1 : 0;
+  ip->stair = ip->shared_exp ? 0 : 1;
+  for (int m = 0; m < 3; ++m)
+    for (int j = 1; j < count[m]; ++j)
+      if (!(nu[first[m] + j] - nu[first[m] + j - 1] > 2.0 * ip->band)) ip->stair = 0;
   // Bound on ln of the product of the three maps' denominators in the
   // unclamped SPEC_FE path: its largest value over the simplex of weights,
   // taken at a vertex (w_i = 1, the other two 0).
@@ -168,7 +174,8 @@ void interp_params(const wcns_desc* d, InterpParams* ip) {
     }
   }
   ip->fast_fe = (ip->shared_exp && B < 600.0 && prod_ok) ? 1 : 0;
-  ip->xa = 0.0;
+  ip->xa = (double)std::min(2.0L * d->xi * 64.0L / std::log(2.0L),
+                            (long double)std::numeric_limits<double>::max());
   ip->xsh = 0;
   std::fill(ip->Pd, ip->Pd + 10, 0.0);
   std::fill(ip->Pa, ip->Pa + 7, 0.0);
@@ -178,7 +185,6 @@ void interp_params(const wcns_desc* d, InterpParams* ip) {
   // The maps' variables and polynomials (InterpParams, fe_map_poly), in long
   // double with the steepness that the rounded xa stands for.
   const long double ln2 = std::log(2.0L);
-  ip->xa = (double)(2.0L * d->xi * 64.0L / ln2);
   const long double x2 = (long double)ip->xa * ln2 / 64.0L;
   // ln of the product of the three denominators at xsh = 0: largest at a
   // vertex of the simplex, and above the sum of the three maps' own least

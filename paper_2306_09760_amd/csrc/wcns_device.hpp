@@ -34,19 +34,32 @@ namespace wcns {
 // Weight choice codes (same values as wcns_weights in wcns.h).
 enum : int { WJS = 0, WZ = 1, WFE = 2, WPFE = 3, WLIN = 4 };
 
-// Compile-time specialisation of the interpolation.  SPEC_FE is the paper's
-// configuration (FE weights on Z weights with p = 2, one shared exponential
-// per map); SPEC_GENERIC switches on the runtime parameters.
-// SPEC_FE: FE weights on p = 2 Z weights with one exponential per map
-// (fast_fe); SPEC_FE_SAT: the same weights where every term takes its own
-// saturating tanh (large xi, shared_exp = 0); SPEC_GENERIC: every choice.
-enum : int { SPEC_GENERIC = 0, SPEC_FE = 1, SPEC_FE_SAT = 2 };
+// Compile-time specialisation of the interpolation (spec_of chooses):
+//   SPEC_FE       FE weights on p = 2 Z weights, one exponential per map (fast_fe);
+//   SPEC_FE_SAT   the same at a steepness where each map is a staircase but for
+//                 a narrow band around its null points (stair);
+//   SPEC_JS, SPEC_Z  JS weights, Z weights with p = 2;
+//   SPEC_PFE      SPEC_FE's weights outside the band of App. A, Z inside;
+//   SPEC_GENERIC  every choice, from the run-time parameters.
+enum : int {
+  SPEC_GENERIC = 0,
+  SPEC_FE = 1,
+  SPEC_FE_SAT = 2,
+  SPEC_JS = 3,
+  SPEC_Z = 4,
+  SPEC_PFE = 5
+};
+// Specialisations that read the exponential's table from LDS.
+constexpr bool spec_table(int spec) {
+  return spec == SPEC_FE || spec == SPEC_FE_SAT || spec == SPEC_PFE;
+}
 
 // Uniform parameters of the interpolation, passed by value to kernels.
 struct InterpParams {
   double eps;       // eq. 11 / eq. 14
   double xi;        // steepness of eq. 20
   double cv;        // PFE band (App. A)
+  double band;      // 20 / xi (fe_stair)
   // Per term j of the three maps (g0: 0..2, g1: 3..6, g2: 7..9), with the null
   // points nu_j = kappa*(psi_{i,j} + psi_{i,j-1}) and a reference point c_i per
   // map (the mean of its null points):
@@ -66,12 +79,14 @@ struct InterpParams {
   // maps at offsets 0, 3, 7 of Pd and 0, 2, 5 of Pa and Pb
   double Pd[10], Pa[7], Pb[7];
   double kap[10];   // the k_j (the adjoint)
-  double xa;        // 2 xi 64 / ln 2 (exp2_tab)
-  int xsh;          // the shift of X_0 and X_1 (fast_fe)
+  double xa;        // 2 xi 64 / ln 2 (exp2_tab: fast_fe, stair)
+  int xsh;          // the shift of X_0 and X_1 (fast_fe; 0 for stair)
   int weights;      // WJS .. WLIN
   int zpow;         // exponent p of eq. 14 (1..4)
   int shared_exp;   // 1: one exponential per map (xi * max|nu - c| < 300)
   int weno;         // 1: K, C2 hold the Table B.2 maps (WENO family)
+  int stair;        // 1: shared_exp = 0 and each map's null points increase by
+                    //    more than twice the band
   int fast_fe;      // 1: shared_exp and the unclamped products of the
                     //    SPEC_FE path stay below e^600 (see fe_map_poly)
 };
@@ -217,7 +232,7 @@ __device__ __forceinline__ double exp2_tab_entry(int k, int xsh) {
   return __builtin_bit_cast(double, t - ((unsigned long long)(unsigned)((k << 14) + (xsh << 20)) << 32));
 }
 
-// X = 2^(w a / 64 - xsh), w in [0, 1], for the FE maps: a = 2 xi 64 / ln 2, so
+// X = 2^(w a / 64 - xsh), |w| <= 1 and |w a| < 2^17, for the FE maps: a = 2 xi 64 / ln 2, so
 // X = 2^-xsh e^(2 xi w).  w a = n + f with n an integer, f exact but for one
 // rounding of its own size (both from fused products, so no reduction in two
 // parts is needed), 2^(f/64) - 1 for |f| <= 1/2 by a degree-4 polynomial, and
@@ -389,6 +404,74 @@ struct FamWcns {
   static constexpr double dr1 = 10.0, dr2 = 5.0;  // d_1 / d_0, d_2 / d_0
 };
 
+// um plus FAM::scale times the mean of x0, x1, x2 under the FE images of the
+// Z weights w0, w1, w2 (which sum to one, so the third map's variable is the
+// product of the other two's, with no third exponential or reciprocal).
+template <class FAM>
+__device__ __forceinline__ double fe_mean(const InterpParams& P, double w0, double w1, double w2,
+                                          double um, double x0, double x1, double x2,
+                                          const double* xt) {
+#pragma clang fp contract(off)
+  const double X0 = exp2_tab(w0, P.xa, xt), X1 = exp2_tab(w1, P.xa, xt);
+  // g_k = n_k / e_k; the normalised weights g_k / sum_l g_l over the
+  // common denominator e_0 e_1 e_2 (fe_map_poly): one reciprocal.
+  double e0, e1, e2;
+  const double n0 = fe_map_poly<3>(w0, X0, P.Pd, P.Pa, P.Pb, &e0);
+  const double n1 = fe_map_poly<4>(w1, X1, P.Pd + 3, P.Pa + 2, P.Pb + 2, &e1);
+  const double n2 = fe_map_poly<3>(w2, X0 * X1, P.Pd + 7, P.Pa + 5, P.Pb + 5, &e2);
+  // T_k = n_k prod_{l != k} e_l: T_0 = A e_2, T_1 = B e_2, T_2 = C
+  const double A = n0 * e1, B = n1 * e0, C = n2 * (e0 * e1);
+  const double num = __builtin_fma(e2, __builtin_fma(A, x0, B * x1), C * x2);
+  // (rcp1: its error is relative to the distance from um)
+  return __builtin_fma(FAM::scale * num, rcp1(__builtin_fma(e2, A + B, C)), um);
+}
+
+// g(w) of one map at a steepness where every tanh is saturated unless w lies
+// within P.band = 20 / xi of a null point (K holds the null points, in
+// increasing order and more than two bands apart: InterpParams::stair): w
+// below the first, the level 2 (a_0 + .. + a_j) above null point j, w above
+// the last (eq. 20; exact, where the sum of the saturated terms rounds).
+// Within a band (and for a NaN) that null point's tanh is taken, every other
+// one is saturated: one exponential and one reciprocal per map for the lanes
+// that need it, where each term used to test and take its own (and the
+// kernel ran at four waves per SIMD instead of five): 512 tubes at xi = 1e6,
+// two steps 0.374 -> 0.291 ms.
+template <int NT>
+__device__ __forceinline__ double fe_stair(double w, const double (&a)[NT], const double (&b)[NT],
+                                           const double* K, const InterpParams& P,
+                                           const double* xt) {
+  double g = w, level = 0.0;
+  bool near = false;
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const double d = w - K[j];
+    level += 2.0 * a[j];
+    g = d > 0.0 ? (j + 1 < NT ? level : w) : g;
+    near = near || !(__builtin_fabs(d) >= P.band);
+  }
+  if (near) {
+    // (the empty asm has the differences taken again here, instead of held in
+    // registers by every lane)
+    double v = w;
+    asm volatile("" : "+v"(v));
+    double x = v, A = 0.0;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const double d = v - K[j];
+      const bool in = __builtin_fabs(d) < P.band;
+      x = in ? d : x;
+      A = in ? (b[j] == 0.0 ? a[j] : __builtin_fma(b[j], v, a[j])) : A;
+    }
+    // tanh x - 1 = -2 e / (1 + e) above the null point, tanh x + 1 = 2 e / (1 +
+    // e) at and below it, e = exp(-2 |x|)
+    // (from the table: few constants to hold; a NaN stays one)
+    const double e = exp2_tab(-__builtin_fabs(x), P.xa, xt);
+    const double c = 2.0 * A * (e * rcp(1.0 + e));
+    g = x > 0.0 ? g - c : g + c;
+  }
+  return g;
+}
+
 // The nonlinear weights of eq. 11 / 14 (+ FE map, eq. 20; PFE switch) from
 // the regularised smoothness indicators b_k = IS_k + eps (so that
 // tau = |IS_0 - IS_2| = |b_0 - b_2|), applied to the candidates of eq. 5.  The
@@ -397,7 +480,7 @@ struct FamWcns {
 // sum): the weights sum to one, so the result is um plus the weighted mean
 // distance, the weights' rounding errors multiply distances instead of
 // values, and a flat stencil returns um itself.  The FE branch serves either
-// family (FAM); the generic branch is the WCNS one.
+// family (FAM); the others are the WCNS one.
 // Bound by FP64 VALU issue: one task of two interpolations takes 219 VALU
 // instructions in the batch kernel (195 of them FP64), 266 with the Z weights
 // as sums times products, a reciprocal for the third map's variable, a
@@ -407,15 +490,14 @@ struct FamWcns {
 // 0.366 ms, the 3D 256^3 step 11.27 -> 10.00 ms, a 2D 512^2 WENO-FE step
 // 0.165 -> 0.153 ms (one box, both sides in turn); the value's error against
 // quadruple precision went from 6e-16 to 0.3-1.3e-16 rms.
-// xt: the exp2_tab_entry table in LDS (SPEC_FE only).
+// xt: the exp2_tab_entry table in LDS (spec_table only).
 template <int SPEC = SPEC_GENERIC, class FAM = FamWcns>
 __device__ __forceinline__ double weigh5(const InterpParams& P, double um, double x0, double x1,
                                          double x2, double b0, double b1, double b2,
                                          const double* xt = nullptr) {
 // every fused operation is written out, so that tiles of any shape round alike
 #pragma clang fp contract(off)
-  constexpr bool FE = (SPEC == SPEC_FE);
-  if constexpr (FE) {
+  if constexpr (SPEC == SPEC_FE || SPEC == SPEC_FE_SAT) {
     // Z weights (p = 2) over the common denominator: alpha_k b_0^2 b_1^2 b_2^2
     // = d_k (b_0^2 b_1^2 b_2^2 + tau^2 times the other two squares), here
     // divided by d_0 (the ratios d_k / d_0 are small integers; the
@@ -431,38 +513,43 @@ __device__ __forceinline__ double weigh5(const InterpParams& P, double um, doubl
     const double z2 = FAM::dr2 * __builtin_fma(t2, p01, p);
     const double zi = rcp(z0 + z1 + z2);
     const double w0 = z0 * zi, w1 = z1 * zi, w2 = z2 * zi;
-    // The Z weights sum to one, so the third map's variable is the product
-    // of the other two's, with no third exponential or reciprocal.
-    const double X0 = exp2_tab(w0, P.xa, xt), X1 = exp2_tab(w1, P.xa, xt);
-    // g_k = n_k / e_k; the normalised weights g_k / sum_l g_l over the
-    // common denominator e_0 e_1 e_2 (fe_map_poly): one reciprocal.
-    double e0, e1, e2;
-    const double n0 = fe_map_poly<3>(w0, X0, P.Pd, P.Pa, P.Pb, &e0);
-    const double n1 = fe_map_poly<4>(w1, X1, P.Pd + 3, P.Pa + 2, P.Pb + 2, &e1);
-    const double n2 = fe_map_poly<3>(w2, X0 * X1, P.Pd + 7, P.Pa + 5, P.Pb + 5, &e2);
-    // T_k = n_k prod_{l != k} e_l: T_0 = A e_2, T_1 = B e_2, T_2 = C
-    const double A = n0 * e1, B = n1 * e0, C = n2 * (e0 * e1);
-    const double num = __builtin_fma(e2, __builtin_fma(A, x0, B * x1), C * x2);
-    // (rcp1: its error is relative to the distance from um)
-    return __builtin_fma(FAM::scale * num, rcp1(__builtin_fma(e2, A + B, C)), um);
-  }
-  if constexpr (SPEC == SPEC_FE_SAT) {
-    // Z weights (p = 2) over the common denominator as above, then each map
-    // term by term (tanh_sat: +-1 without an exponential once saturated).
-    const double tau = __builtin_fabs(b0 - b2);
-    const double t2 = tau * tau;
-    const double q0 = b0 * b0, q1 = b1 * b1, q2 = b2 * b2;
-    const double z0 = D0 * (q0 + t2) * (q1 * q2);
-    const double z1 = D1 * (q1 + t2) * (q0 * q2);
-    const double z2 = D2 * (q2 + t2) * (q0 * q1);
-    const double zi = rcp(z0 + z1 + z2);
-    const double g0 = fe_g0<SPEC_GENERIC>(z0 * zi, P), g1 = fe_g1<SPEC_GENERIC>(z1 * zi, P),
-                 g2 = fe_g2<SPEC_GENERIC>(z2 * zi, P);
+    if constexpr (SPEC == SPEC_FE) return fe_mean<FAM>(P, w0, w1, w2, um, x0, x1, x2, xt);
+    // Each map is a staircase (exactly: no rounding of the sum of its terms);
+    // a lane near a null point takes the terms themselves.
+    const double g0 = fe_stair<3>(w0, kG0a, kG0b, P.K, P, xt);
+    const double g1 = fe_stair<4>(w1, kG1a, kG1b, P.K + 3, P, xt);
+    const double g2 = fe_stair<3>(w2, kG2a, kG2b, P.K + 7, P, xt);
     const double ginv = rcp(g0 + g1 + g2);
     return __builtin_fma(0.125 * ginv, __builtin_fma(g0, x0, __builtin_fma(g1, x1, g2 * x2)), um);
   }
+  if constexpr (SPEC == SPEC_JS) {
+    // alpha_k = d_k / b_k^2 times b_0^2 b_1^2 b_2^2: no reciprocal but the sum's
+    const double m0 = b1 * b2, m1 = b0 * b2, m2 = b0 * b1;
+    const double z0 = m0 * m0, z1 = 10.0 * (m1 * m1), z2 = 5.0 * (m2 * m2);
+    const double zi = rcp(z0 + z1 + z2);
+    const double num = __builtin_fma(z0, x0, __builtin_fma(z1, x1, z2 * x2));
+    return __builtin_fma(0.125 * num, zi, um);
+  }
+  if constexpr (SPEC == SPEC_Z || SPEC == SPEC_PFE) {
+    // alpha_k = d_k (1 + (tau / b_k)^2) with one reciprocal for the three 1 / b_k
+    const double m0 = b1 * b2, m1 = b0 * b2, m2 = b0 * b1;
+    const double tr = (b0 - b2) * rcp(b0 * m0);
+    const double a0 = tr * m0, a1 = tr * m1, a2 = tr * m2;
+    const double z0 = __builtin_fma(a0, a0, 1.0), z1 = 10.0 * __builtin_fma(a1, a1, 1.0),
+                 z2 = 5.0 * __builtin_fma(a2, a2, 1.0);
+    const double zi = rcp(z0 + z1 + z2);
+    if constexpr (SPEC == SPEC_Z) {
+      const double num = __builtin_fma(z0, x0, __builtin_fma(z1, x1, z2 * x2));
+      return __builtin_fma(0.125 * num, zi, um);
+    }
+    const double w0 = z0 * zi, w1 = z1 * zi, w2 = z2 * zi;
+    if (__builtin_fabs(w0 - D0) <= P.cv && __builtin_fabs(w1 - D1) <= P.cv &&
+        __builtin_fabs(w2 - D2) <= P.cv)
+      return __builtin_fma(0.125, __builtin_fma(w0, x0, __builtin_fma(w1, x1, w2 * x2)), um);
+    return fe_mean<FAM>(P, w0, w1, w2, um, x0, x1, x2, xt);
+  }
   double a0, a1, a2;
-  if (!FE && P.weights == WJS) {
+  if (P.weights == WJS) {
     const double r0 = rcp(b0), r1 = rcp(b1), r2 = rcp(b2);
     a0 = D0 * r0 * r0;
     a1 = D1 * r1 * r1;
@@ -471,8 +558,7 @@ __device__ __forceinline__ double weigh5(const InterpParams& P, double um, doubl
     const double tau = __builtin_fabs(b0 - b2);
     double q0 = tau * rcp(b0), q1 = tau * rcp(b1), q2 = tau * rcp(b2);
     double p0 = q0, p1 = q1, p2 = q2;
-    const int zpow = FE ? 2 : P.zpow;
-    for (int k = 1; k < zpow; ++k) {
+    for (int k = 1; k < P.zpow; ++k) {
       p0 *= q0;
       p1 *= q1;
       p2 *= q2;
@@ -484,8 +570,8 @@ __device__ __forceinline__ double weigh5(const InterpParams& P, double um, doubl
   const double inv = rcp(a0 + a1 + a2);
   double w0 = a0 * inv, w1 = a1 * inv, w2 = a2 * inv;
 
-  bool map = FE || (P.weights == WFE);
-  if (!FE && P.weights == WPFE) {
+  bool map = P.weights == WFE;
+  if (P.weights == WPFE) {
     const bool inside = __builtin_fabs(w0 - D0) <= P.cv && __builtin_fabs(w1 - D1) <= P.cv &&
                         __builtin_fabs(w2 - D2) <= P.cv;
     map = !inside;
@@ -518,7 +604,6 @@ template <int SPEC = SPEC_GENERIC>
 __device__ __forceinline__ void interp5_pair(const InterpParams& P, const double (&u)[6],
                                              double* left, double* right,
                                              const double* xt = nullptr) {
-  constexpr bool FE = (SPEC == SPEC_FE);
   const double d0 = u[1] - u[0], d1 = u[2] - u[1], d2 = u[3] - u[2], d3 = u[4] - u[3],
                d4 = u[5] - u[4];
   const double s0 = d1 - d0, s1 = d2 - d1, s2 = d3 - d2, s3 = d4 - d3;
@@ -531,7 +616,7 @@ __device__ __forceinline__ void interp5_pair(const InterpParams& P, const double
                x2 = __builtin_fma(4.0, f2, s2);
   const double y0 = __builtin_fma(4.0, g0, s3), y1 = __builtin_fma(4.0, g1, s2),
                y2 = __builtin_fma(4.0, g2, s1);
-  if (!FE && P.weights == WLIN) {
+  if (SPEC == SPEC_GENERIC && P.weights == WLIN) {
     *left = __builtin_fma(0.125, D0 * x0 + D1 * x1 + D2 * x2, u[2]);
     *right = __builtin_fma(0.125, D0 * y0 + D1 * y1 + D2 * y2, u[3]);
     return;

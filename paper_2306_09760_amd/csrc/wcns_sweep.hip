@@ -216,7 +216,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
     }
   }
   double xv = 0.0;
-  if constexpr (SPEC == SPEC_FE) {
+  if constexpr (spec_table(SPEC)) {
     if (tid < 64) xv = exp2_tab_entry(tid, a.ip.xsh);
   }
 #pragma unroll
@@ -227,7 +227,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
       for (int v = 0; v < NV; ++v) sU[v * SV + idx] = buf[it][v];
     }
   }
-  if constexpr (SPEC == SPEC_FE) {
+  if constexpr (spec_table(SPEC)) {
     if (tid < 64) sX[tid] = xv;
   }
   __syncthreads();
@@ -500,10 +500,11 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
 #define WCNS_REG_WAVES 5
 #endif
 constexpr int sweep_waves(int nv, int tmw, int spec) {
-  return spec == SPEC_GENERIC ? 1
-         : spec != SPEC_FE    ? 4
-         : sweep_reg(nv, tmw) ? WCNS_REG_WAVES
-                              : 6;
+  return spec == SPEC_GENERIC                ? 1
+         : spec == SPEC_JS || spec == SPEC_Z ? 6
+         : spec == SPEC_FE_SAT               ? (sweep_reg(nv, tmw) ? 4 : 5)
+         : sweep_reg(nv, tmw)                ? WCNS_REG_WAVES
+                                             : 6;
 }
 
 template <int NV, int DIR, bool BATCH, int SPEC, int TM, int W>
@@ -556,11 +557,14 @@ template <int NV, int DIR, bool BATCH, int TM, int W>
 static hipError_t sweep_go(const SweepArgs& a, const BatchArgs& b, const TileGeom& g, int mode,
                            hipStream_t s) {
   const size_t lds = sizeof(double) * SweepLayout<NV, TM, W>::lds_doubles;
-  const int spec = spec_of(a.ip);
-  if (spec == SPEC_FE) return sweep_launch<NV, DIR, BATCH, SPEC_FE, TM, W>(a, b, g, mode, lds, s);
-  if (spec == SPEC_FE_SAT)
-    return sweep_launch<NV, DIR, BATCH, SPEC_FE_SAT, TM, W>(a, b, g, mode, lds, s);
-  return sweep_launch<NV, DIR, BATCH, SPEC_GENERIC, TM, W>(a, b, g, mode, lds, s);
+  switch (spec_of(a.ip)) {
+    case SPEC_FE: return sweep_launch<NV, DIR, BATCH, SPEC_FE, TM, W>(a, b, g, mode, lds, s);
+    case SPEC_FE_SAT: return sweep_launch<NV, DIR, BATCH, SPEC_FE_SAT, TM, W>(a, b, g, mode, lds, s);
+    case SPEC_JS: return sweep_launch<NV, DIR, BATCH, SPEC_JS, TM, W>(a, b, g, mode, lds, s);
+    case SPEC_Z: return sweep_launch<NV, DIR, BATCH, SPEC_Z, TM, W>(a, b, g, mode, lds, s);
+    case SPEC_PFE: return sweep_launch<NV, DIR, BATCH, SPEC_PFE, TM, W>(a, b, g, mode, lds, s);
+    default: return sweep_launch<NV, DIR, BATCH, SPEC_GENERIC, TM, W>(a, b, g, mode, lds, s);
+  }
 }
 
 template <int NV, int DIR, bool BATCH>
