@@ -653,9 +653,9 @@ struct FamWeno {
 // weno5 with FE weights on p = 2 Z weights through the fast path of weigh5
 // (Table B.1 ideal weights, Table B.2 maps); xt: the exp2_tab_entry table in
 // LDS.  With f_k and s_k as in interp5_pair, B_k = f_k^2 + 13/12 s_k^2 and
-// the candidate is c + f_k / 2 + s_k / 12.
-__device__ __forceinline__ double weno5_fe(const InterpParams& P, double a, double b, double c,
-                                           double e, double f, const double* xt) {
+// the candidate is c + f_k / 2 + s_k / 12.  eps: added to the B_k.
+__device__ __forceinline__ double weno5_fe(const InterpParams& P, double eps, double a, double b,
+                                           double c, double e, double f, const double* xt) {
   constexpr double k = 13.0 / 12.0;
   const double d0 = b - a, d1 = c - b, d2 = e - c, d3 = f - e;
   const double s0 = d1 - d0, s1 = d2 - d1, s2 = d3 - d2;
@@ -663,18 +663,18 @@ __device__ __forceinline__ double weno5_fe(const InterpParams& P, double a, doub
                f2 = __builtin_fma(-0.5, s2, d2);
   return weigh5<SPEC_FE, FamWeno>(P, c, __builtin_fma(6.0, f0, s0), __builtin_fma(6.0, f1, s1),
                                   __builtin_fma(6.0, f2, s2),
-                                  __builtin_fma(f0, f0, __builtin_fma(k * s0, s0, P.eps)),
-                                  __builtin_fma(f1, f1, __builtin_fma(k * s1, s1, P.eps)),
-                                  __builtin_fma(f2, f2, __builtin_fma(k * s2, s2, P.eps)), xt);
+                                  __builtin_fma(f0, f0, __builtin_fma(k * s0, s0, eps)),
+                                  __builtin_fma(f1, f1, __builtin_fma(k * s1, s1, eps)),
+                                  __builtin_fma(f2, f2, __builtin_fma(k * s2, s2, eps)), xt);
 }
 
 // Finite-difference WENO5 reconstruction at x_{i+1/2} from the point values
 // (f_{i-2}, ..., f_{i+2}) = (a, b, c, e, f): Jiang-Shu smoothness indicators
 // (through first differences, as for the WCNS indicators), JS / Z weights
 // with the ideal weights of Table B.1, the FE map of Table B.2 (P.K and P.C2
-// hold its null points), PFE switch.
-__device__ __forceinline__ double weno5(const InterpParams& P, double a, double b, double c,
-                                        double e, double f) {
+// hold its null points), PFE switch.  eps: added to the indicators.
+__device__ __forceinline__ double weno5(const InterpParams& P, double eps, double a, double b,
+                                        double c, double e, double f) {
   const double q0 = (1.0 / 6.0) * (2.0 * a - 7.0 * b + 11.0 * c);
   const double q1 = (1.0 / 6.0) * (-b + 5.0 * c + 2.0 * e);
   const double q2 = (1.0 / 6.0) * (2.0 * c + 5.0 * e - f);
@@ -688,13 +688,13 @@ __device__ __forceinline__ double weno5(const InterpParams& P, double a, double 
   const double B2 = (13.0 / 12.0) * s22 * s22 + 0.25 * s12 * s12;
   double a0, a1, a2;
   if (P.weights == WJS) {
-    const double r0 = rcp(B0 + P.eps), r1 = rcp(B1 + P.eps), r2 = rcp(B2 + P.eps);
+    const double r0 = rcp(B0 + eps), r1 = rcp(B1 + eps), r2 = rcp(B2 + eps);
     a0 = E0 * r0 * r0;
     a1 = E1 * r1 * r1;
     a2 = E2 * r2 * r2;
   } else {
     const double tau = __builtin_fabs(B0 - B2);
-    const double t0 = tau * rcp(B0 + P.eps), t1 = tau * rcp(B1 + P.eps), t2 = tau * rcp(B2 + P.eps);
+    const double t0 = tau * rcp(B0 + eps), t1 = tau * rcp(B1 + eps), t2 = tau * rcp(B2 + eps);
     double p0 = t0, p1 = t1, p2 = t2;
     for (int k = 1; k < P.zpow; ++k) {
       p0 *= t0;
@@ -954,13 +954,6 @@ __device__ __forceinline__ unsigned long long wave_max_bits(unsigned long long v
   const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, 63);
   const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 63);
   return ((unsigned long long)hi << 32) | lo;
-}
-
-// Wave speed |u_DIR| + c of one state along DIR.
-template <int ND, int DIR>
-__device__ __forceinline__ double dir_speed(const double* U, double gamma) {
-  const Prim<ND> q = primitives<ND>(U, gamma);
-  return __builtin_fabs(q.vel[DIR]) + sqrt_pos(gamma * q.p * q.ir);
 }
 
 // True if the state is finite and (Euler) rho > 0 and p > 0.

@@ -1,21 +1,33 @@
 // Directional sweep of the filtered embedded WENO scheme of App. B on gfx950:
 // finite-difference WENO5 with Lax-Friedrichs flux splitting and a
-// conservative difference, same tile organisation as the WCNS sweep.
+// conservative difference, on the tiles of the WCNS sweep.
 //
-// A workgroup of 256 lanes owns TM midpoints (TM*W = 128) of W adjacent
-// columns and writes the TL = TM - 1 nodes between them.  Phases:
-//   load     the TM+5 nodes of every column into LDS, ghosts applied;
-//   node     physical flux F(U) and wave speed |u_n| + c of every node;
-//   mid      Roe state (vel, H, c, ic) of nodes m, m+1 and the splitting speed
-//            alpha_m = max of the wave speed over the six stencil nodes;
-//   recon    one task per (side, field, midpoint): the field-v projection of
-//            f+ = (F + alpha U)/2 on the left-biased stencil (side 0) or of
-//            f- = (F - alpha U)/2 on the mirrored one (side 1), then the WENO5
-//            reconstruction;
-//   flux     F~ = R (f+^ + f-^) per midpoint;
+// A workgroup of 128 lanes owns TM midpoints (TM W = 128) of W adjacent columns,
+// one midpoint per lane, and writes the TL = TM - 1 nodes between them.
+// Along x the lines are packed end to end (TileGeom::lines, 3 ghost slots per
+// side).  Phases:
+//   load     the TM+5 nodes of every column, ghosts applied; each lane takes
+//            the physical flux and the wave speed |u_n| + c of the nodes it has
+//            loaded, and node, flux (but for the density's, a momentum row) and
+//            speed go to LDS;
+//   mid      the lane's Roe state of nodes m, m+1 (in registers) and splitting
+//            speed alpha, the largest wave speed of the six stencil nodes;
+//   recon    per field: its projections of F and U at the six nodes, the split
+//            fluxes F + alpha U and F - alpha U (twice those of the splitting:
+//            the half goes into the difference, eps is taken four times), and
+//            the WENO5 reconstruction of the first from the left-biased, of the
+//            second from the mirrored stencil;
+//   flux     2 F~ = R (f+^ + f-^), the lane's own values;
 //   diff     -(F~_{i+1/2} - F~_{i-1/2}) / h, written as R, R+= or a stage.
-// LDS (doubles): sU[NV][TM+5][W] | sF[NV][TM+5][W] | sL[TM+5][W] | sR[ND+3][TMW]
-// | sA[TMW] | sW[2 NV][TMW] | the 64-entry exp table (FE specialisation).
+// Bound by FP64 VALU issue.  One lane reconstructs both sides from projections
+// of F and U, 12 NV products per field where a task per side, field and
+// midpoint took 30 NV; load | mid and flux | diff are the only barriers.
+// Against 256 lanes on 128 midpoints with two tasks per field and midpoint in
+// five phases: residual 2D 512^2 0.0598 -> 0.0445 ms, 1024^2 0.179 -> 0.127,
+// 2048^2 0.635 -> 0.436, 3D 128^3 0.892 -> 0.497 ms.  256 lanes on 256
+// midpoints are 1 % faster from 1024^2 on, and 13 % slower in 3D.
+// LDS (doubles): sU[NV][TM+5][W] | sF[NV-1][TM+5][W] | sL[TM+5][W] |
+// sW[NV][128] | the exp table (FE specialisation).
 #include <hip/hip_runtime.h>
 
 #include "wcns_internal.hpp"
@@ -26,50 +38,56 @@ namespace wcns {
 template <int NV, int TM, int W>
 struct WenoLayout {
   static constexpr int ND = NV > 1 ? NV - 2 : 1;
-  static constexpr int NR = NV > 1 ? NV - 2 + 3 : 0;  // vel[ND], H, c, ic
   static constexpr int TN = TM + 5;
   static constexpr int TMW = TM * W;
   static constexpr int SV = TN * W;
   static constexpr int LW = W == 1 ? 0 : W == 2 ? 1 : W == 4 ? 2 : 3;
   static constexpr size_t lds_doubles =
-      (size_t)(2 * NV + 1) * SV + (size_t)(NR + 1 + 2 * NV) * TMW + 64;
-  static_assert(TMW == 128, "WENO tiles hold 128 midpoints");
+      (size_t)(NV > 1 ? 2 * NV : 1) * SV + (size_t)NV * TMW + 64;
+  static_assert(TMW == 128, "one midpoint per lane");
 };
 
+// Register budget: the FE specialisation fits five waves per SIMD, the
+// run-time weights four.
+constexpr int weno_waves(int spec) { return spec == SPEC_FE ? 5 : 4; }
+
 template <int NV, int DIR, int SPEC, int TM, int W>
-__global__ void __launch_bounds__(256) weno_sweep_kernel(SweepArgs a, TileGeom g, int mode) {
+__global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(weno_waves(SPEC))))
+    weno_sweep_kernel(SweepArgs a, TileGeom g, int mode) {
   using L = WenoLayout<NV, TM, W>;
-  constexpr int ND = L::ND, NR = L::NR, TMW = L::TMW, SV = L::SV, LW = L::LW;
-  constexpr int NT = 256;
+  constexpr int ND = L::ND, TMW = L::TMW, SV = L::SV, LW = L::LW;
+  constexpr int NT = TMW;
   constexpr int TL = TM - 1;
+  constexpr int G = 3;  // ghosts on each side
   extern __shared__ double smem[];
   double* sU = smem;
-  double* sF = sU + NV * SV;
-  double* sL = sF + NV * SV;
-  double* sR = sL + SV;
-  double* sA = sR + NR * TMW;
-  double* sW = sA + TMW;
-  double* sX = sW + 2 * NV * TMW;  // exp2_tab_entry
+  double* sF = sU + NV * SV;                   // rows 1 .. NV-1 of the flux
+  double* sL = sF + (NV - 1) * SV;
+  double* sW = NV > 1 ? sL + SV : sU + SV;
+  double* sX = sW + NV * TMW;  // exp2_tab_entry
   const int tid = threadIdx.x;
 
   if ((int64_t)blockIdx.x >= g.ntiles) return;
   const int64_t tile = xcd_tile(blockIdx.x, g.ntiles);
-  int64_t base, N, stride;
+  int64_t base = 0, N, stride = 1, i0;
   int ncol = 1;
-  // column groups fastest: adjacent groups split the same cache lines
-  // tile < 2^31 (checked at launch): multiply-shift divisions
-  const uint32_t t32 = (uint32_t)tile;
-  const uint32_t r32 = g.dxg.div(t32);
-  const uint32_t o32 = g.dseg.div(r32);
-  const int64_t xg = t32 - r32 * (uint32_t)g.xgroups;
-  const int64_t seg = r32 - o32 * (uint32_t)g.segs;
-  const int64_t other = o32;
-  const int64_t i0 = seg * TL;
+  BatchTile bt{};
+  bool near = true;  // the tile spans at most two lines
   if constexpr (DIR == 0) {
     N = a.n[0];
-    base = other * N;
-    stride = 1;
+    i0 = tile * TL;
+    bt = line_tile(i0, N, g.lines, G, TL, g.inv_line);
+    near = bt.p1 <= bt.p0 + 1;
   } else {
+    // column groups fastest: adjacent groups split the same cache lines
+    // tile < 2^31 (checked at launch): multiply-shift divisions
+    const uint32_t t32 = (uint32_t)tile;
+    const uint32_t r32 = g.dxg.div(t32);
+    const uint32_t o32 = g.dseg.div(r32);
+    const int64_t xg = t32 - r32 * (uint32_t)g.xgroups;
+    const int64_t seg = r32 - o32 * (uint32_t)g.segs;
+    const int64_t other = o32;
+    i0 = seg * TL;
     const int64_t x0 = xg * W;
     ncol = (int)((a.n[0] - x0) < W ? (a.n[0] - x0) : W);
     if constexpr (DIR == 1) {
@@ -85,159 +103,191 @@ __global__ void __launch_bounds__(256) weno_sweep_kernel(SweepArgs a, TileGeom g
   const double dt = (mode >= MODE_STAGE) ? *a.dt : 0.0;
   const int64_t nb = i0 - 3;  // position of LDS node 0; midpoint t is m = i0 - 1 + t
 
-  // load
+  // load: every global read issued before the first LDS write
+  constexpr int NIT = (SV + NT - 1) / NT;
+  static_assert(NIT <= 2, "a tile holds at most two nodes per lane");
+  double buf[NIT][NV];
+#pragma unroll
+  for (int it = 0; it < NIT; ++it) {
+    const int idx = tid + it * NT;
+    if (idx < SV) {
+      const int k = idx >> LW, c = idx & (W - 1);
+      const int cc = c < ncol ? c : ncol - 1;
+      int64_t gi;
+      if constexpr (DIR == 0) {
+        const BatchSlot sl =
+            near ? batch_slot_near(bt, k - G) : line_slot(nb + k, N, g.lines, G, g.inv_line);
+        // slots outside every line load a ghost; no output node uses them
+        const int j = sl.j < -G ? -G : (sl.j >= sl.n + G ? sl.n + G - 1 : sl.j);
+        gi = sl.o + bc_index_near(j, sl.n, a.bc);
+      } else {
+        gi = base + bc_index(nb + k, N, a.bc) * stride + cc;
+      }
+#pragma unroll
+      for (int v = 0; v < NV; ++v) buf[it][v] = a.U[v * a.npts + gi];
+    }
+  }
+  // the lane's output node in a tile of packed lines (-1: none or a ghost slot)
+  int64_t onode = -1;
+  if constexpr (DIR == 0) {
+    if (tid < TL) {
+      const BatchSlot sl =
+          near ? batch_slot_near(bt, tid) : line_slot(i0 + tid, N, g.lines, G, g.inv_line);
+      if (sl.j >= 0 && sl.j < sl.n) onode = sl.o + sl.j;
+    }
+  }
   if constexpr (SPEC == SPEC_FE) {
     if (tid < 64) sX[tid] = exp2_tab_entry(tid, a.ip.xsh);
   }
-  for (int idx = tid; idx < SV; idx += NT) {
-    const int k = idx >> LW, c = idx & (W - 1);
-    const int cc = c < ncol ? c : ncol - 1;
-    const int64_t gi = base + bc_index(nb + k, N, a.bc) * stride + cc;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) sU[v * SV + idx] = a.U[v * a.npts + gi];
+  for (int it = 0; it < NIT; ++it) {
+    const int idx = tid + it * NT;
+    if (idx < SV) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) sU[v * SV + idx] = buf[it][v];
+      if constexpr (NV > 1) {
+        const double* U = buf[it];
+        const Prim<ND> q = primitives<ND>(U, a.pp.gamma);
+        const double vn = q.vel[DIR];
+#pragma unroll
+        for (int k = 0; k < ND; ++k)
+          sF[k * SV + idx] = k == DIR ? __builtin_fma(U[1 + k], vn, q.p) : U[1 + k] * vn;
+        sF[ND * SV + idx] = (U[ND + 1] + q.p) * vn;
+        sL[idx] = __builtin_fabs(vn) + sqrt_pos(a.pp.gamma * q.p * q.ir);
+      }
+    }
   }
   __syncthreads();
 
   const bool proj = (NV > 1) && a.pp.charproj;
+  const double eps4 = 4.0 * a.ip.eps;
+  RoeState<ND> rsq{};
+  double al = 0.0;
   if constexpr (NV > 1) {
-    // node fluxes and wave speeds
-    for (int idx = tid; idx < SV; idx += NT) {
-      double U[NV], F[NV];
+    al = sL[tid];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) U[v] = sU[v * SV + idx];
-      euler_flux<ND, DIR>(U, a.pp.gamma, F);
+    for (int j = 1; j < 6; ++j) al = __builtin_fmax(al, sL[tid + j * W]);
+    if (proj) {
+      const double* u = sU + tid + 2 * W;
+      double UA[NV], UB[NV];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) sF[v * SV + idx] = F[v];
-      sL[idx] = dir_speed<ND, DIR>(U, a.pp.gamma);
-    }
-    __syncthreads();
-    // Roe state and splitting speed per midpoint
-#pragma unroll 1
-    for (int q = tid; q < TMW; q += NT) {
-      double al = sL[q];
-#pragma unroll
-      for (int j = 1; j < 6; ++j) al = __builtin_fmax(al, sL[q + j * W]);
-      sA[q] = al;
-      if (proj) {
-        const double* u = sU + q + 2 * W;
-        double UA[NV], UB[NV];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          UA[v] = u[v * SV];
-          UB[v] = u[v * SV + W];
-        }
-        const RoeState<ND> rs = roe_average<ND>(UA, UB, a.pp.gamma);
-        double* rr = sR + q;
-#pragma unroll
-        for (int k = 0; k < ND; ++k) rr[k * TMW] = rs.vel[k];
-        rr[(ND + 0) * TMW] = rs.H;
-        rr[(ND + 1) * TMW] = rs.c;
-        rr[(ND + 2) * TMW] = rs.ic;
+      for (int v = 0; v < NV; ++v) {
+        UA[v] = u[v * SV];
+        UB[v] = u[v * SV + W];
       }
+      rsq = roe_average<ND>(UA, UB, a.pp.gamma);
     }
-    __syncthreads();
   }
 
-  // reconstruction, one task per (side, field, midpoint)
+  // reconstruction of each field at the lane's midpoint
 #pragma unroll 1
-  for (int q = tid; q < 2 * NV * TMW; q += NT) {
-    const int slot = q / TMW;
-    const int rem = q - slot * TMW;
-    const int side = slot >= NV;
-    const int v = side ? slot - NV : slot;
-    double w[5];
+  for (int v = 0; v < NV; ++v) {
+    double wp[5], wm[5];  // F + alpha U of nodes 0 .. 4, F - alpha U of nodes 5 .. 1
     if constexpr (NV == 1) {
-      const double s = side ? 0.5 * (a.pp.adv - __builtin_fabs(a.pp.adv))
-                            : 0.5 * (a.pp.adv + __builtin_fabs(a.pp.adv));
+      const double sp = a.pp.adv + __builtin_fabs(a.pp.adv);
+      const double sm = a.pp.adv - __builtin_fabs(a.pp.adv);
 #pragma unroll
-      for (int s5 = 0; s5 < 5; ++s5) w[s5] = s * sU[rem + (side ? 5 - s5 : s5) * W];
+      for (int j = 0; j < 5; ++j) {
+        wp[j] = sp * sU[tid + j * W];
+        wm[j] = sm * sU[tid + (5 - j) * W];
+      }
     } else {
-      const double al = side ? -sA[rem] : sA[rem];
-      // the split flux of node k: (F + al U) / 2, component e
-      auto split = [&](int e, int k) { return 0.5 * __builtin_fma(al, sU[e * SV + k], sF[e * SV + k]); };
+      double wu[6], wf[6];
+      const double* u = sU + tid;
+      const double* fr = sU + (1 + DIR) * SV + tid;  // the density's flux
+      const double* f = sF + tid;                    // row e - 1: component e
       if (proj) {
-        const double* rr = sR + rem;
         if (v >= 2 && v < NV - 1) {  // shear field: X_ax - vel_ax X_rho
           const int ax = tangential_axis<ND, DIR>(v - 2);
-          const double va = rr[ax * TMW];
+          double va = rsq.vel[0];
 #pragma unroll
-          for (int s5 = 0; s5 < 5; ++s5) {
-            const int k = rem + (side ? 5 - s5 : s5) * W;
-            w[s5] = __builtin_fma(-va, split(0, k), split(1 + ax, k));
+          for (int k = 1; k < ND; ++k) va = (ax == k) ? rsq.vel[k] : va;
+#pragma unroll
+          for (int j = 0; j < 6; ++j) {
+            wu[j] = __builtin_fma(-va, u[j * W], u[(1 + ax) * SV + j * W]);
+            wf[j] = __builtin_fma(-va, fr[j * W], f[ax * SV + j * W]);
           }
         } else {
           RoeState<ND> rs;
+          // recomputed per field from vel and ic (the empty asm hides that
+          // they are loop-invariant)
 #pragma unroll
-          for (int k = 0; k < ND; ++k) rs.vel[k] = rr[k * TMW];
-          rs.ic = rr[(ND + 2) * TMW];
+          for (int k = 0; k < ND; ++k) {
+            rs.vel[k] = rsq.vel[k];
+            asm volatile("" : "+v"(rs.vel[k]));
+          }
+          rs.ic = rsq.ic;
+          asm volatile("" : "+v"(rs.ic));
           roe_derived<ND>(rs, a.pp.gamma);
           double l[NV];
           field_row<ND, DIR>(rs, v, l);
+          project_stencil<NV, SV, W>(u, l, wu);
 #pragma unroll
-          for (int s5 = 0; s5 < 5; ++s5) {
-            const int k = rem + (side ? 5 - s5 : s5) * W;
-            double acc = l[0] * split(0, k);
+          for (int j = 0; j < 6; ++j) wf[j] = l[0] * fr[j * W];
 #pragma unroll
-            for (int e = 1; e < NV; ++e) acc = __builtin_fma(l[e], split(e, k), acc);
-            w[s5] = acc;
+          for (int e = 1; e < NV; ++e) {
+            const lds_cptr fe = lds_row(f + (e - 1) * SV);
+#pragma unroll
+            for (int j = 0; j < 6; ++j) wf[j] = __builtin_fma(l[e], fe[j * W], wf[j]);
           }
         }
       } else {
+        const double* fv = v == 0 ? fr : f + (v - 1) * SV;
 #pragma unroll
-        for (int s5 = 0; s5 < 5; ++s5) w[s5] = split(v, rem + (side ? 5 - s5 : s5) * W);
+        for (int j = 0; j < 6; ++j) {
+          wu[j] = u[v * SV + j * W];
+          wf[j] = fv[j * W];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 5; ++j) {
+        wp[j] = __builtin_fma(al, wu[j], wf[j]);
+        wm[j] = __builtin_fma(-al, wu[5 - j], wf[5 - j]);
       }
     }
+    double r;
     if constexpr (SPEC == SPEC_FE)
-      sW[q] = weno5_fe(a.ip, w[0], w[1], w[2], w[3], w[4], sX);
+      r = weno5_fe(a.ip, eps4, wp[0], wp[1], wp[2], wp[3], wp[4], sX) +
+          weno5_fe(a.ip, eps4, wm[0], wm[1], wm[2], wm[3], wm[4], sX);
     else
-      sW[q] = weno5(a.ip, w[0], w[1], w[2], w[3], w[4]);
+      r = weno5(a.ip, eps4, wp[0], wp[1], wp[2], wp[3], wp[4]) +
+          weno5(a.ip, eps4, wm[0], wm[1], wm[2], wm[3], wm[4]);
+    sW[v * TMW + tid] = r;
   }
-  __syncthreads();
 
-  // midpoint flux F~ = R (f+^ + f-^) into sW rows 0..NV-1
-#pragma unroll 1
-  for (int q = tid; q < TMW; q += NT) {
-    double G[NV], F[NV];
+  // twice the midpoint flux, 2 F~ = R (f+^ + f-^), of the lane's own midpoint
+  if constexpr (NV > 1) {
+    if (proj) {
+      double Gv[NV], F[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) G[v] = sW[v * TMW + q] + sW[(NV + v) * TMW + q];
-    if constexpr (NV > 1) {
-      if (proj) {
-        RoeState<ND> rs;
-        const double* rr = sR + q;
+      for (int v = 0; v < NV; ++v) Gv[v] = sW[v * TMW + tid];
+      unproject<ND, DIR>(rsq, Gv, F);
 #pragma unroll
-        for (int k = 0; k < ND; ++k) rs.vel[k] = rr[k * TMW];
-        rs.H = rr[(ND + 0) * TMW];
-        rs.c = rr[(ND + 1) * TMW];
-        rs.ic = rr[(ND + 2) * TMW];
-        roe_derived<ND>(rs, a.pp.gamma);
-        unproject<ND, DIR>(rs, G, F);
-      } else {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) F[v] = G[v];
-      }
-    } else {
-      F[0] = G[0];
+      for (int v = 0; v < NV; ++v) sW[v * TMW + tid] = F[v];
     }
-#pragma unroll
-    for (int v = 0; v < NV; ++v) sW[v * TMW + q] = F[v];
   }
   __syncthreads();
 
   // conservative difference
-#pragma unroll 1
-  for (int q = tid; q < TL * W; q += NT) {
-    const int t = q >> LW, c = q & (W - 1);
-    const int64_t i = i0 + t;
-    if (i >= N || c >= ncol) continue;
-    double res[NV], Un[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const double* fv = sW + v * TMW + q;   // F~ of midpoint t at fv[0], t + 1 at fv[W]
-      res[v] = -a.ih * (fv[W] - fv[0]);
-      Un[v] = sU[v * SV + q + 3 * W];
-    }
-    emit_rt<NV>(mode, a, base + i * stride + c, a.npts, res, Un, dt);
+  if (tid >= TL * W) return;
+  const int t = tid >> LW, c = tid & (W - 1);
+  int64_t i = i0 + t;
+  if constexpr (DIR == 0) {
+    if (onode < 0) return;
+    base = onode;
+    i = 0;
+  } else {
+    if (i >= N || c >= ncol) return;
   }
+  double res[NV], Un[NV];
+  const double hih = -0.5 * a.ih;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const double* fv = sW + v * TMW + tid;  // 2 F~ of midpoint t at fv[0], t + 1 at fv[W]
+    res[v] = hih * (fv[W] - fv[0]);
+    Un[v] = sU[v * SV + tid + 3 * W];
+  }
+  emit_rt<NV>(mode, a, base + i * stride + c, a.npts, res, Un, dt);
 }
 
 // --------------------------------------------------------------- launchers --
@@ -258,13 +308,19 @@ static hipError_t weno_go(const SweepArgs& a, int mode, hipStream_t s) {
   g.dseg = fast_div((uint32_t)g.segs);
   const int64_t others = DIR == 0 ? a.n[1] * a.n[2] : (DIR == 1 ? a.n[2] : a.n[1]);
   g.ntiles = g.segs * g.xgroups * others;
+  if (DIR == 0) {  // packed x-lines, 3 ghost slots per side
+    const int64_t len = a.n[0] + 6;
+    g.lines = others;
+    g.inv_line = 1.0 / (double)len;
+    g.ntiles = (others * len + g.tl - 1) / g.tl;
+  }
   if (g.ntiles > 0x7fffffff) return hipErrorInvalidConfiguration;
   if (spec_of(a.ip) == SPEC_FE)
     hipLaunchKernelGGL((weno_sweep_kernel<NV, DIR, SPEC_FE, TM, W>), dim3((unsigned)g.ntiles),
-                       dim3(256), sizeof(double) * L::lds_doubles, s, a, g, mode);
+                       dim3(L::TMW), sizeof(double) * L::lds_doubles, s, a, g, mode);
   else
     hipLaunchKernelGGL((weno_sweep_kernel<NV, DIR, SPEC_GENERIC, TM, W>), dim3((unsigned)g.ntiles),
-                       dim3(256), sizeof(double) * L::lds_doubles, s, a, g, mode);
+                       dim3(L::TMW), sizeof(double) * L::lds_doubles, s, a, g, mode);
   return hipGetLastError();
 }
 
