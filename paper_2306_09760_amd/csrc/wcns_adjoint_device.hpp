@@ -286,8 +286,8 @@ template <int ND, int DIR>
 __device__ __forceinline__ void flux_speed_vjp(const double* U, const Prim<ND>& q, double gamma,
                                                double c, const double* Fb, double lamb,
                                                double* Ub) {
-  const double E = U[ND + 1], vn = q.vel[DIR];
-  double vnb = Fb[ND + 1] * (E + q.p);
+  const double vn = q.vel[DIR];
+  double vnb = Fb[ND + 1] * q.ep;
 #pragma unroll
   for (int k = 0; k < ND; ++k) vnb = __builtin_fma(Fb[1 + k], U[1 + k], vnb);
   const double Eb = Fb[ND + 1] * vn;
@@ -344,8 +344,8 @@ __device__ __forceinline__ void roe_vjp(const double* UA, const double* UB, doub
   const Prim<ND> B = primitives<ND>(UB, gamma);
   const double s = sqrt_pos(UB[0] * A.ir);
   const double wA = rcp(1.0 + s), wB = s * wA;
-  const double HA = (UA[ND + 1] + A.p) * A.ir;
-  const double HB = (UB[ND + 1] + B.p) * B.ir;
+  const double HA = A.ep * A.ir;
+  const double HB = B.ep * B.ir;
   double wb = rb.H * (HA - HB);
 #pragma unroll
   for (int k = 0; k < ND; ++k) wb = __builtin_fma(rb.vel[k], A.vel[k] - B.vel[k], wb);

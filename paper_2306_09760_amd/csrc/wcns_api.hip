@@ -526,16 +526,37 @@ wcns_status wcns_cfl_dt(wcns_plan* plan, const double* U, double cfl, double* dt
 }
 
 namespace {
+// The whole step in one launch where that serves the plan (line_step_ok): sets
+// *done.  U1, U2: arrays for the stage states, or null.
+wcns_status line_step(const wcns_plan* P, double* U, double* U1, double* U2, const double* dt_dev,
+                      double cfl, double* dtw, int32_t* status_dev, int stages, hipStream_t s,
+                      bool* done) {
+  *done = P->d.ndim == 1 && P->d.scheme == WCNS_SCHEME_WCNS &&
+          line_step_ok(P->nv, P->npts, P->d.diff, stages);
+  if (!*done) return WCNS_OK;
+  SweepArgs a;
+  sweep_common(P, 0, &a);
+  a.status = status_dev;
+  WCNS_HIP(launch_line_step(P->nv, a, U, U1, U2, dt_dev, cfl, std::fabs(P->d.adv_speed[0]) * P->ih[0],
+                            dtw, stages, s),
+           "line step launch");
+  return WCNS_OK;
+}
+
 // One SSP-RK3 step of U in place with the stage states in W1, W2, the
 // residual accumulator of the 2D/3D sweeps in Racc, and (for a cfl-limited
 // step) the block maxima in partial and dt in dtw.
 wcns_status rk3_step_bufs(wcns_plan* plan, double* U, double* W1, double* W2, double* Racc,
                           double* partial, double* dtw, const double* dt_dev, double cfl,
-                          int32_t* status_dev, void* stream) {
+                          int32_t* status_dev, void* stream, bool keep_stages = false) {
   hipStream_t s = (hipStream_t)stream;
   const double* dt = dt_dev;
+  if (!dt && !(cfl > 0.0)) return fail(WCNS_EINVAL, "cfl must be > 0 when dt_dev is NULL");
+  bool done;
+  const wcns_status ls = line_step(plan, U, keep_stages ? W1 : nullptr, keep_stages ? W2 : nullptr,
+                                   dt_dev, cfl, dtw, status_dev, 3, s, &done);
+  if (done) return ls;
   if (!dt) {
-    if (!(cfl > 0.0)) return fail(WCNS_EINVAL, "cfl must be > 0 when dt_dev is NULL");
     WCNS_HIP(launch_cfl(plan->nv, plan->d.ndim, U, plan->npts, plan->d.gamma, plan->ih,
                         plan->d.adv_speed, cfl, partial, plan->ncfl, dtw, s),
              "cfl launch");
@@ -550,11 +571,12 @@ wcns_status rk3_step_bufs(wcns_plan* plan, double* U, double* W1, double* W2, do
 
 // rk3_step_bufs with the buffers in the caller's workspace.
 wcns_status rk3_step_into(wcns_plan* plan, double* U, double* W1, double* W2, void* work,
-                          const double* dt_dev, double cfl, int32_t* status_dev, void* stream) {
+                          const double* dt_dev, double cfl, int32_t* status_dev, void* stream,
+                          bool keep_stages = false) {
   char* w = (char*)work;
   return rk3_step_bufs(plan, U, W1, W2, (double*)(w + plan->off_R),
                        (double*)(w + plan->off_partial), (double*)(w + plan->off_dt), dt_dev, cfl,
-                       status_dev, stream);
+                       status_dev, stream, keep_stages);
 }
 
 // The device array behind wcns_rk3_step_noalloc (each GPU holds its own copy
@@ -636,7 +658,7 @@ wcns_status wcns_rk3_step_stages(wcns_plan* plan, double* U, double* U1, double*
   g_err.clear();
   if (!plan || !U || !U1 || !U2 || !work) return fail(WCNS_EINVAL, "NULL argument");
   if (U1 == U || U2 == U || U1 == U2) return fail(WCNS_EINVAL, "U, U1 and U2 must be distinct");
-  return rk3_step_into(plan, U, U1, U2, work, dt_dev, cfl, status_dev, stream);
+  return rk3_step_into(plan, U, U1, U2, work, dt_dev, cfl, status_dev, stream, true);
 }
 
 wcns_status wcns_rk4_step(wcns_plan* plan, double* U, void* work, const double* dt_dev, double cfl,
@@ -652,9 +674,12 @@ wcns_status wcns_rk4_step(wcns_plan* plan, double* U, void* work, const double* 
   double* Racc = (double*)(w + plan->off_R);
   const int64_t len = plan->nv * plan->npts;
   const double* dt = dt_dev;
+  double* dtw = (double*)(w + plan->off_dt);
+  if (!dt && !(cfl > 0.0)) return fail(WCNS_EINVAL, "cfl must be > 0 when dt_dev is NULL");
+  bool done;
+  const wcns_status ls = line_step(plan, U, nullptr, nullptr, dt_dev, cfl, dtw, status_dev, 4, s, &done);
+  if (done) return ls;
   if (!dt) {
-    if (!(cfl > 0.0)) return fail(WCNS_EINVAL, "cfl must be > 0 when dt_dev is NULL");
-    double* dtw = (double*)(w + plan->off_dt);
     WCNS_HIP(launch_cfl(plan->nv, plan->d.ndim, U, plan->npts, plan->d.gamma, plan->ih,
                         plan->d.adv_speed, cfl, (double*)(w + plan->off_partial), plan->ncfl, dtw, s),
              "cfl launch");

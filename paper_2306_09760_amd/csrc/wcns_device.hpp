@@ -726,6 +726,11 @@ __device__ __forceinline__ double weno5(const InterpParams& P, double eps, doubl
 // ------------------------------------------------------------------ Euler --
 // State layout in registers: [rho, m_0 .. m_{ND-1}, E].
 
+// From here to the state check no product is fused but where it is written
+// out (contract(off)): left to the compiler, which of two products a sum
+// fuses depends on what else a kernel does with them, and every kernel that
+// takes a step is to round alike.
+
 // a . b and |v|^2, every fused product written out (which product is rounded
 // by itself is part of the result, and the tiles of every shape and the
 // weight statistics are to agree).
@@ -748,28 +753,33 @@ template <int ND>
 struct Prim {
   double ir;        // 1/rho
   double vel[ND];
-  double p;
+  double p, ep;     // pressure, E + p
 };
 
 template <int ND, bool NEWTON2 = false>
 __device__ __forceinline__ Prim<ND> primitives(const double* U, double gamma) {
+#pragma clang fp contract(off)
   Prim<ND> q;
   q.ir = rcp<NEWTON2>(U[0]);
 #pragma unroll
   for (int k = 0; k < ND; ++k) q.vel[k] = U[1 + k] * q.ir;
-  q.p = (gamma - 1.0) * __builtin_fma(-0.5, dot<ND>(U + 1, q.vel), U[ND + 1]);
+  const double ei = __builtin_fma(-0.5, dot<ND>(U + 1, q.vel), U[ND + 1]);
+  q.p = (gamma - 1.0) * ei;
+  q.ep = __builtin_fma(gamma - 1.0, ei, U[ND + 1]);
   return q;
 }
 
 // Physical flux along DIR (eq. 32).
 template <int ND, int DIR>
 __device__ __forceinline__ void euler_flux(const double* U, double gamma, double* F) {
+#pragma clang fp contract(off)
   const Prim<ND> q = primitives<ND>(U, gamma);
   const double vn = q.vel[DIR];
   F[0] = U[1 + DIR];
 #pragma unroll
-  for (int k = 0; k < ND; ++k) F[1 + k] = U[1 + k] * vn + (k == DIR ? q.p : 0.0);
-  F[ND + 1] = (U[ND + 1] + q.p) * vn;
+  for (int k = 0; k < ND; ++k)
+    F[1 + k] = k == DIR ? __builtin_fma(U[1 + k], vn, q.p) : U[1 + k] * vn;
+  F[ND + 1] = q.ep * vn;
 }
 
 // Roe-averaged quantities that define the eigenvectors between two nodes.
@@ -783,6 +793,7 @@ struct RoeState {
 // as roe_average (so tiles may keep only vel, H, c and ic).
 template <int ND>
 __device__ __forceinline__ void roe_derived(RoeState<ND>& r, double gamma) {
+#pragma clang fp contract(off)
   r.q2h = 0.5 * norm2<ND>(r.vel);
   r.b1 = (gamma - 1.0) * r.ic * r.ic;
   r.b2 = r.q2h * r.b1;
@@ -791,6 +802,7 @@ __device__ __forceinline__ void roe_derived(RoeState<ND>& r, double gamma) {
 template <int ND, bool NEWTON2 = false>
 __device__ __forceinline__ RoeState<ND> roe_average(const double* UA, const double* UB,
                                                     double gamma) {
+#pragma clang fp contract(off)
   const Prim<ND> A = primitives<ND, NEWTON2>(UA, gamma);
   const Prim<ND> B = primitives<ND, NEWTON2>(UB, gamma);
   // weights sqrt(rho_A) / (sqrt(rho_A) + sqrt(rho_B)) and the same for B,
@@ -800,8 +812,8 @@ __device__ __forceinline__ RoeState<ND> roe_average(const double* UA, const doub
   RoeState<ND> r;
 #pragma unroll
   for (int k = 0; k < ND; ++k) r.vel[k] = __builtin_fma(wA, A.vel[k], wB * B.vel[k]);
-  const double HA = (UA[ND + 1] + A.p) * A.ir;
-  const double HB = (UB[ND + 1] + B.p) * B.ir;
+  const double HA = A.ep * A.ir;
+  const double HB = B.ep * B.ir;
   r.H = __builtin_fma(wA, HA, wB * HB);
   r.q2h = 0.5 * norm2<ND>(r.vel);
   r.c = sqrt_pos<NEWTON2>((gamma - 1.0) * (r.H - r.q2h));
@@ -843,6 +855,7 @@ __device__ __forceinline__ void project(const RoeState<ND>& r, const double* U, 
 // written as a dot product so that a stencil costs NV operations per node.
 template <int ND, int DIR>
 __device__ __forceinline__ void field_row(const RoeState<ND>& r, int v, double (&l)[ND + 2]) {
+#pragma clang fp contract(off)
   if (v == 1) {  // entropy: rho - theta
     l[0] = 1.0 - r.b2;
 #pragma unroll
@@ -862,6 +875,7 @@ __device__ __forceinline__ void field_row(const RoeState<ND>& r, int v, double (
 
 template <int ND, int DIR>
 __device__ __forceinline__ void unproject(const RoeState<ND>& r, const double* W, double* U) {
+#pragma clang fp contract(off)
   const double ac = W[0] + W[ND + 1];
   const double sum = ac + W[1];
   const double cd = r.c * (W[ND + 1] - W[0]);
@@ -883,6 +897,7 @@ __device__ __forceinline__ void unproject(const RoeState<ND>& r, const double* W
 template <int ND, int DIR>
 __device__ __forceinline__ void llf_flux2(const double* UL, const double* UR, double gamma,
                                           double* F) {
+#pragma clang fp contract(off)
   constexpr int NV = ND + 2;
   const Prim<ND> L = primitives<ND>(UL, gamma);
   const Prim<ND> R = primitives<ND>(UR, gamma);
@@ -897,7 +912,7 @@ __device__ __forceinline__ void llf_flux2(const double* UL, const double* UR, do
   for (int k = 0; k < ND; ++k)
     F[1 + k] = k == DIR ? __builtin_fma(UL[1 + k], vL, __builtin_fma(UR[1 + k], vR, L.p + R.p))
                         : __builtin_fma(UL[1 + k], vL, UR[1 + k] * vR);
-  F[ND + 1] = __builtin_fma(UL[ND + 1] + L.p, vL, (UR[ND + 1] + R.p) * vR);
+  F[ND + 1] = __builtin_fma(L.ep, vL, R.ep * vR);
 #pragma unroll
   for (int v = 0; v < NV; ++v) F[v] = __builtin_fma(-alpha, UR[v] - UL[v], F[v]);
 }
@@ -906,6 +921,7 @@ __device__ __forceinline__ void llf_flux2(const double* UL, const double* UR, do
 template <int NV, int DIR>
 __device__ __forceinline__ void node_flux(const PhysParams& PP, const double (&U)[NV],
                                           double (&F)[NV]) {
+#pragma clang fp contract(off)
   if constexpr (NV == 1) {
     F[0] = PP.adv * U[0];
   } else {
@@ -917,11 +933,12 @@ __device__ __forceinline__ void node_flux(const PhysParams& PP, const double (&U
 // caller adds |a_d| / h_d).
 template <int ND>
 __device__ __forceinline__ double wave_rate(const double* U, double gamma, const double* ih) {
+#pragma clang fp contract(off)
   const Prim<ND> q = primitives<ND>(U, gamma);
   const double c = sqrt_pos(gamma * q.p * q.ir);
   double s = 0.0;
 #pragma unroll
-  for (int k = 0; k < ND; ++k) s += (__builtin_fabs(q.vel[k]) + c) * ih[k];
+  for (int k = 0; k < ND; ++k) s = __builtin_fma(__builtin_fabs(q.vel[k]) + c, ih[k], s);
   return s;
 }
 

@@ -142,6 +142,15 @@ hipError_t launch_axpy_state(double* y, const double* x, double a, int64_t n,
                              hipStream_t stream);
 hipError_t launch_lincomb(double* out, const double* x, double ax, const double* y, double ay,
                           const double* dt, double ydt, int64_t n, hipStream_t stream);
+// A whole step of a short 1D WCNS problem in one launch (wcns_line.hip), bitwise
+// the step of the sweeps: whether it serves these sizes, and the launch.  s: the
+// sweep's arguments (n, bc, diff, ih, ip, pp, status); dt null: cfl / max rate
+// (advection: adv_rate), left in *dt_out; U1, U2: the RK3 stage states' arrays or
+// null; stages: 3 (SSP-RK3) or 4 (eq. 16).
+bool line_step_ok(int nv, int64_t n, int diff, int stages);
+hipError_t launch_line_step(int nv, const SweepArgs& s, double* U, double* U1, double* U2,
+                            const double* dt, double cfl, double adv_rate, double* dt_out,
+                            int stages, hipStream_t stream);
 // The filtered embedded WENO sweep of App. B (wcns_weno.hip).
 hipError_t launch_weno_sweep(int nv, int dir, const SweepArgs& a, int mode, hipStream_t stream);
 // Weight histograms of one direction's interpolations (wcns_stats.hip).

@@ -152,7 +152,7 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(weno_w
 #pragma unroll
         for (int k = 0; k < ND; ++k)
           sF[k * SV + idx] = k == DIR ? __builtin_fma(U[1 + k], vn, q.p) : U[1 + k] * vn;
-        sF[ND * SV + idx] = (U[ND + 1] + q.p) * vn;
+        sF[ND * SV + idx] = q.ep * vn;
         sL[idx] = __builtin_fabs(vn) + sqrt_pos(a.pp.gamma * q.p * q.ir);
       }
     }
