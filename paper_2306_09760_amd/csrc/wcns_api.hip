@@ -282,7 +282,11 @@ struct wcns_plan {
   InterpParams ip;
   double ih[3];
   int ncfl;
+  int npartial;  // entries of `partial`
   size_t off_W1, off_W2, off_R, off_partial, off_dt, off_A1, off_A2, bytes;
+  bool one_launch_stages() const {
+    return d.scheme == WCNS_SCHEME_WCNS && stage_step_ok(d.ndim, nv, d.n);
+  }
 };
 
 struct wcns_batch_plan {
@@ -458,7 +462,9 @@ wcns_status wcns_plan_create(const wcns_desc* desc, wcns_plan** plan) {
     auto it = g_tune_cache.find(k);
     if (it != g_tune_cache.end()) std::tie(P->tm, P->seg, P->bw) = it->second;
   }
-  P->ncfl = cfl_blocks(P->npts);
+  P->ncfl = P->npartial = cfl_blocks(P->npts);
+  if (P->one_launch_stages())
+    P->npartial = std::max(P->ncfl, (int)stage_partials(P->d.n, P->d.diff));
   const size_t state = sizeof(double) * P->nv * P->npts;
   size_t o = 0;
   P->off_W1 = o; o += align256(state);
@@ -466,7 +472,8 @@ wcns_status wcns_plan_create(const wcns_desc* desc, wcns_plan** plan) {
   P->off_R = o; o += align256(state);
   P->off_A1 = o; o += align256(state);
   P->off_A2 = o; o += align256(state);
-  P->off_partial = o; o += align256(sizeof(double) * P->ncfl);
+  if (P->one_launch_stages() && P->d.ndim == 3) o += 2 * align256(state);  // (see stage_step)
+  P->off_partial = o; o += align256(sizeof(double) * P->npartial);
   P->off_dt = o; o += 256;
   P->bytes = o;
   *plan = P;
@@ -569,11 +576,50 @@ wcns_status rk3_step_bufs(wcns_plan* plan, double* U, double* W1, double* W2, do
   return WCNS_OK;
 }
 
+// The step with one launch per stage: the directional residuals in 2 ndim
+// arrays from RA on, one after the other (W2, R, A1, A2 and, in 3D, two more of
+// the workspace), U2 kept when given.
+wcns_status stage_step(const wcns_plan* P, double* U, double* U1, double* U2, double* RA,
+                       double* partial, double* dtw, const double* dt_dev, double cfl,
+                       int32_t* status_dev, hipStream_t s) {
+  StageStep p{};
+  for (int d = 0; d < P->d.ndim; ++d) sweep_common(P, d, &p.a[d]);
+  p.U = U;
+  p.U1 = U1;
+  p.U2 = U2;
+  p.rstride = (int64_t)(align256(sizeof(double) * P->nv * P->npts) / sizeof(double));
+  p.RA = RA;
+  p.RB = RA + P->d.ndim * p.rstride;
+  p.partial = partial;
+  p.dt = dt_dev;
+  p.dt_out = dtw;
+  p.cfl = cfl;
+  p.status = status_dev;
+  WCNS_HIP(launch_stage_step(P->d.ndim, p, s), "stage launch");
+  return WCNS_OK;
+}
+
+// Arrays [p, p + bytes) and [q, q + bytes) overlap.
+bool overlaps(const void* p, size_t pb, const void* q, size_t qb) {
+  const char* a = (const char*)p;
+  const char* b = (const char*)q;
+  return a < b + qb && b < a + pb;
+}
+
 // rk3_step_bufs with the buffers in the caller's workspace.
 wcns_status rk3_step_into(wcns_plan* plan, double* U, double* W1, double* W2, void* work,
                           const double* dt_dev, double cfl, int32_t* status_dev, void* stream,
                           bool keep_stages = false) {
   char* w = (char*)work;
+  // (stage arrays of the caller's that lie in the workspace meet the residuals there)
+  const size_t sb = sizeof(double) * plan->nv * plan->npts;
+  const bool inside = keep_stages && (overlaps(W1, sb, work, plan->bytes) || overlaps(W2, sb, work, plan->bytes));
+  if (plan->one_launch_stages() && !inside) {
+    if (!dt_dev && !(cfl > 0.0)) return fail(WCNS_EINVAL, "cfl must be > 0 when dt_dev is NULL");
+    return stage_step(plan, U, W1, keep_stages ? W2 : nullptr, (double*)(w + plan->off_W2),
+                      (double*)(w + plan->off_partial), (double*)(w + plan->off_dt), dt_dev, cfl,
+                      status_dev, (hipStream_t)stream);
+  }
   return rk3_step_bufs(plan, U, W1, W2, (double*)(w + plan->off_R),
                        (double*)(w + plan->off_partial), (double*)(w + plan->off_dt), dt_dev, cfl,
                        status_dev, stream, keep_stages);
@@ -638,6 +684,13 @@ wcns_status wcns_rk3_step_noalloc(wcns_plan* plan, double* U, const double* dt_d
   if (st != WCNS_OK) return st;
   char* w = (char*)base;
   const size_t state = align256(sizeof(double) * plan->nv * plan->npts);
+  if (plan->one_launch_stages()) {
+    const size_t op = (1 + 2 * (size_t)plan->d.ndim) * state;
+    const size_t od = op + align256(sizeof(double) * plan->npartial);
+    if (od + 256 <= kScratchBytes)
+      return stage_step(plan, U, (double*)w, nullptr, (double*)(w + state), (double*)(w + op),
+                        (double*)(w + od), dt_dev, cfl, status_dev, (hipStream_t)stream);
+  }
   double* W1 = (double*)w;
   double* W2 = (double*)(w + state);
   size_t o = 2 * state;
@@ -764,13 +817,6 @@ wcns_status wcns_residual_adjoint(wcns_plan* plan, const double* U, const double
 }
 
 namespace {
-// Arrays [p, p + bytes) and [q, q + bytes) overlap.
-bool overlaps(const void* p, size_t pb, const void* q, size_t qb) {
-  const char* a = (const char*)p;
-  const char* b = (const char*)q;
-  return a < b + qb && b < a + pb;
-}
-
 // The reverse step writes lambda in place while neighbouring tiles still read
 // the states under the stencil, and keeps its stage cotangents in the
 // workspace: lambda must not overlap Un, U1, U2 or the workspace, and the

@@ -151,6 +151,26 @@ bool line_step_ok(int nv, int64_t n, int diff, int stages);
 hipError_t launch_line_step(int nv, const SweepArgs& s, double* U, double* U1, double* U2,
                             const double* dt, double cfl, double adv_rate, double* dt_out,
                             int stages, hipStream_t stream);
+// An SSP-RK3 step of a small 2D or 3D WCNS-Euler problem with one launch per
+// stage (wcns_stage.hip), bitwise the step of the sweeps: whether it serves
+// these sizes, the entries of `partial` and the launch.
+struct StageStep {
+  SweepArgs a[3];        // each direction's n, bc, diff, ih, ip, pp, npts
+  double* U;             // state, in place
+  double* U1;            // first stage state (written)
+  double* U2;            // second one, or null
+  double* RA;            // directional residuals, ndim arrays rstride apart each
+  double* RB;
+  int64_t rstride;
+  double* partial;
+  const double* dt;      // or null: cfl / max rate, left in *dt_out
+  double* dt_out;
+  double cfl;
+  int32_t* status;
+};
+bool stage_step_ok(int ndim, int nv, const int64_t n[3]);
+int64_t stage_partials(const int64_t n[3], int diff);
+hipError_t launch_stage_step(int ndim, const StageStep& p, hipStream_t stream);
 // The filtered embedded WENO sweep of App. B (wcns_weno.hip).
 hipError_t launch_weno_sweep(int nv, int dir, const SweepArgs& a, int mode, hipStream_t stream);
 // Weight histograms of one direction's interpolations (wcns_stats.hip).
