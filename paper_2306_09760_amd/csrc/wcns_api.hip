@@ -308,7 +308,11 @@ struct wcns_batch_plan {
   // uses the list only if both still hold)
   const void* list_work = nullptr;
   int list_tm = 0;
-  size_t off_W1, off_W2, off_dtp, off_wmax, off_live, off_nlive, bytes;
+  size_t off_W1, off_W2, off_dtp, off_wmax, off_live, off_nlive, off_pack, bytes;
+  // tiles of the one-launch step (0: too many for it)
+  int32_t* d_pack_p0 = nullptr;
+  int32_t* d_pack_p1 = nullptr;
+  int32_t pack_tiles = 0;
   // graph-captured step
   bool use_graph = false;
   hipStream_t cap_stream = nullptr;
@@ -972,17 +976,18 @@ wcns_status wcns_plan_autotune(wcns_plan* plan, const double* U, void* work, voi
 
 // ------------------------------------------------------------------ batch --
 
-static wcns_status batch_build_tiles(wcns_batch_plan* B) {
-  // Packed tiles over the virtual index space of the problems laid end to
-  // end with 2G ghost slots each (BatchArgs): all tiles are full, so only the
-  // 2G slots per problem compute midpoints that no node uses.
-  const int G = B->d.diff ? 5 : 4;
-  const int TL = B->tm - (B->d.diff ? 5 : 3);
+// Packed tiles of TL slots over the virtual index space of the problems laid end
+// to end with 2G ghost slots each (BatchArgs): all tiles are full, so only the
+// 2G slots per problem compute midpoints that no node uses.
+static int64_t batch_tiles(const wcns_batch_plan* B, int G, int TL) {
+  return (B->h_offset[B->nprob] + 2 * G * B->nprob + TL - 1) / TL;
+}
+
+// Their tables, into device arrays that the caller owns.
+static wcns_status batch_tile_tables(const wcns_batch_plan* B, int G, int TL, int64_t nt,
+                                     int32_t** d_p0, int32_t** d_p1) {
   const int64_t np = B->nprob;
   auto start = [&](int64_t p) { return B->h_offset[p] + 2 * G * p; };
-  const int64_t V = start(np);
-  const int64_t nt = (V + TL - 1) / TL;
-  if (nt > INT32_MAX) return fail(WCNS_EUNSUPPORTED, "batch needs %lld tiles", (long long)nt);
   std::vector<int32_t> tp((size_t)nt), tq((size_t)nt);
   int64_t p = 0, q = 0;  // problems holding the first and the last slot of tile k
   for (int64_t k = 0; k < nt; ++k) {
@@ -992,16 +997,26 @@ static wcns_status batch_build_tiles(wcns_batch_plan* B) {
     tp[(size_t)k] = (int32_t)p;
     tq[(size_t)k] = (int32_t)q;
   }
+  WCNS_HIP(hipMalloc(d_p0, sizeof(int32_t) * tp.size()), "hipMalloc tiles");
+  WCNS_HIP(hipMalloc(d_p1, sizeof(int32_t) * tq.size()), "hipMalloc tiles");
+  WCNS_HIP(hipMemcpy(*d_p0, tp.data(), sizeof(int32_t) * tp.size(), hipMemcpyHostToDevice), "copy tiles");
+  WCNS_HIP(hipMemcpy(*d_p1, tq.data(), sizeof(int32_t) * tq.size(), hipMemcpyHostToDevice), "copy tiles");
+  return WCNS_OK;
+}
+
+static wcns_status batch_build_tiles(wcns_batch_plan* B) {
+  const int G = B->d.diff ? 5 : 4;
+  const int TL = B->tm - (B->d.diff ? 5 : 3);
+  const int64_t nt = batch_tiles(B, G, TL);
+  if (nt > INT32_MAX) return fail(WCNS_EUNSUPPORTED, "batch needs %lld tiles", (long long)nt);
   if (B->d_tile_p0) hipFree(B->d_tile_p0);
   if (B->d_tile_p1) hipFree(B->d_tile_p1);
   B->d_tile_p0 = nullptr;
   B->d_tile_p1 = nullptr;
   B->ntiles = (int32_t)nt;
   B->list_work = nullptr;
-  WCNS_HIP(hipMalloc(&B->d_tile_p0, sizeof(int32_t) * tp.size()), "hipMalloc tiles");
-  WCNS_HIP(hipMalloc(&B->d_tile_p1, sizeof(int32_t) * tq.size()), "hipMalloc tiles");
-  WCNS_HIP(hipMemcpy(B->d_tile_p0, tp.data(), sizeof(int32_t) * tp.size(), hipMemcpyHostToDevice), "copy tiles");
-  WCNS_HIP(hipMemcpy(B->d_tile_p1, tq.data(), sizeof(int32_t) * tq.size(), hipMemcpyHostToDevice), "copy tiles");
+  const wcns_status st = batch_tile_tables(B, G, TL, nt, &B->d_tile_p0, &B->d_tile_p1);
+  if (st != WCNS_OK) return st;
   // one workgroup per tile
   B->grid = B->ntiles;
   if (B->exec) {
@@ -1051,6 +1066,15 @@ wcns_status wcns_batch_plan_create(const wcns_desc* proto, int64_t nprob, const 
     return cleanup(hip_fail(e, "hipMemcpy"));
   if ((st = batch_build_tiles(B)) != WCNS_OK) return cleanup(st);
   {
+    const int G = pack_tile_ghosts(proto->diff), TL = pack_tile_nodes(proto->diff);
+    const int64_t nt = batch_tiles(B, G, TL);
+    if (nt <= pack_max_tiles()) {
+      st = batch_tile_tables(B, G, TL, nt, &B->d_pack_p0, &B->d_pack_p1);
+      if (st != WCNS_OK) return cleanup(st);
+      B->pack_tiles = (int32_t)nt;
+    }
+  }
+  {
     // the most tiles any candidate shape needs (the smallest tile)
     const int G = proto->diff ? 5 : 4;
     const int64_t V = B->h_offset[nprob] + 2 * G * nprob;
@@ -1067,6 +1091,8 @@ wcns_status wcns_batch_plan_create(const wcns_desc* proto, int64_t nprob, const 
   B->off_wmax = o; o += align256(sizeof(unsigned long long) * nprob);
   B->off_live = o; o += align256(sizeof(int32_t) * B->max_tiles);
   B->off_nlive = o; o += 256;
+  // (one-launch steps) two more arrays of maxima and one of times
+  B->off_pack = o; o += B->pack_tiles > 0 ? 3 * align256(sizeof(double) * nprob) : 0;
   B->bytes = o;
   *plan = B;
   return WCNS_OK;
@@ -1080,6 +1106,8 @@ wcns_status wcns_batch_plan_destroy(wcns_batch_plan* B) {
   if (B->d_ih) hipFree(B->d_ih);
   if (B->d_tile_p0) hipFree(B->d_tile_p0);
   if (B->d_tile_p1) hipFree(B->d_tile_p1);
+  if (B->d_pack_p0) hipFree(B->d_pack_p0);
+  if (B->d_pack_p1) hipFree(B->d_pack_p1);
   delete B;
   return WCNS_OK;
 }
@@ -1160,7 +1188,7 @@ static wcns_status batch_step_enqueue(wcns_batch_plan* B, double* U, void* work,
   if (fused_dt)
     WCNS_HIP(launch_batch_dt(b, t_dev, t_end, cfl, wmax, status, nlive, s), "batch dt launch");
   else
-    WCNS_HIP(launch_batch_cfl(U, B->total, b, B->d.gamma, t_dev, t_end, cfl,
+    WCNS_HIP(launch_batch_cfl(U, B->total, b, B->d.gamma, t_dev, t_dev, t_end, cfl,
                               keep_max ? wmax : nullptr, status, nlive, s),
              "batch cfl launch");
   if (rebuild) {
@@ -1189,6 +1217,68 @@ static wcns_status batch_step_enqueue(wcns_batch_plan* B, double* U, void* work,
 // finished stay listed and leave at once.
 static const int32_t kLiveEvery = 4;
 
+// nsteps steps of a batch small enough for one launch per step: each from one of
+// U and W1 to the other, with dt from the maxima that the step before left in one
+// of three arrays (the third being cleared for the step after), and the time from
+// one array to another so that no tile reads what another one writes; the last
+// step leaves it in t_dev.  The live list is kept as the sweeps' steps keep it.
+static wcns_status batch_pack_steps(wcns_batch_plan* B, double* U, void* work, double* t_dev,
+                                    double t_end, double cfl, int32_t nsteps, int32_t* status,
+                                    hipStream_t s) {
+  char* w = (char*)work;
+  const size_t pb = align256(sizeof(double) * B->nprob);
+  unsigned long long* wmax[3] = {(unsigned long long*)(w + B->off_wmax),
+                                 (unsigned long long*)(w + B->off_pack),
+                                 (unsigned long long*)(w + B->off_pack + pb)};
+  double* const time[2] = {t_dev, (double*)(w + B->off_pack + 2 * pb)};
+  int32_t* nlive = (int32_t*)(w + B->off_nlive);
+  double* cur = U;
+  double* const W1 = (double*)(w + B->off_W1);
+  for (int32_t k = 0; k < nsteps; ++k) {
+    SweepArgs a;
+    BatchArgs b;
+    batch_args(B, (double*)(w + B->off_dtp), &a, &b, work);
+    BatchArgs pk = b;
+    pk.tile_p0 = B->d_pack_p0;
+    pk.tile_p1 = B->d_pack_p1;
+    pk.ntiles = B->pack_tiles;
+    const bool last = k + 1 == nsteps, rebuild = k % kLiveEvery == 0;
+    PackDt d{};
+    if (k == 0) {
+      WCNS_HIP(launch_batch_cfl(U, B->total, b, B->d.gamma, t_dev, time[(nsteps - 1) & 1], t_end,
+                                cfl, wmax[0], status, nlive, s),
+               "batch cfl launch");
+    } else {
+      d.wmax = wmax[(k + 2) % 3];
+      d.t_in = time[(nsteps - k) & 1];
+      d.t_out = time[(nsteps - 1 - k) & 1];
+      d.t_end = t_end;
+      d.cfl = cfl;
+      d.nlive = rebuild ? nlive : nullptr;
+    }
+    d.clear = last ? nullptr : wmax[(k + 1) % 3];
+    a.status = status;
+    a.wmax = last ? nullptr : wmax[k % 3];
+    double* to = cur == U ? W1 : U;
+    WCNS_HIP(launch_pack_step(a, pk, d, cur, to, s), "batch step launch");
+    cur = to;
+    if (rebuild) {
+      const wcns_status st = batch_rebuild_live(B, b, work, s);
+      if (st != WCNS_OK) return st;
+    }
+  }
+  if (cur != U)
+    WCNS_HIP(launch_lincomb(U, nullptr, 0.0, cur, 1.0, nullptr, 0.0, 3 * B->total, s), "batch copy");
+  return WCNS_OK;
+}
+
+// One step in place.
+static wcns_status batch_one_step(wcns_batch_plan* B, double* U, void* work, double* t_dev,
+                                  double t_end, double cfl, int32_t* status, hipStream_t s) {
+  if (B->pack_tiles > 0) return batch_pack_steps(B, U, work, t_dev, t_end, cfl, 1, status, s);
+  return batch_step_enqueue(B, U, work, t_dev, t_end, cfl, status, s);
+}
+
 static wcns_status batch_rk3_steps(wcns_batch_plan* B, double* U, void* work, double* t_dev,
                                    double t_end, double cfl, int32_t nsteps, int32_t* status_dev,
                                    int32_t cap, void* stream) {
@@ -1197,6 +1287,8 @@ static wcns_status batch_rk3_steps(wcns_batch_plan* B, double* U, void* work, do
   if (!std::isfinite(t_end)) return fail(WCNS_EINVAL, "t_end must be finite");
   if (nsteps < 0) return fail(WCNS_EINVAL, "nsteps %d < 0", nsteps);
   hipStream_t s = (hipStream_t)stream;
+  if (B->pack_tiles > 0 && cap == 0)
+    return batch_pack_steps(B, U, work, t_dev, t_end, cfl, nsteps, status_dev, s);
   for (int32_t k = 0; k < nsteps; ++k) {
     const wcns_status st = batch_step_enqueue(B, U, work, t_dev, t_end, cfl, status_dev, s, k > 0,
                                               k + 1 < nsteps, k % kLiveEvery == 0, cap);
@@ -1242,7 +1334,7 @@ wcns_status wcns_batch_rk3_step(wcns_batch_plan* B, double* U, void* work, doubl
   if (!(cfl > 0.0)) return fail(WCNS_EINVAL, "cfl must be > 0");
   if (!std::isfinite(t_end)) return fail(WCNS_EINVAL, "t_end must be finite");
   hipStream_t s = (hipStream_t)stream;
-  if (!B->use_graph) return batch_step_enqueue(B, U, work, t_dev, t_end, cfl, status_dev, s);
+  if (!B->use_graph) return batch_one_step(B, U, work, t_dev, t_end, cfl, status_dev, s);
   auto key = std::make_tuple((const void*)U, (const void*)work, (const void*)t_dev, t_end, cfl,
                              (const void*)status_dev, B->tm);
   if (!B->exec || key != B->key) {
@@ -1252,7 +1344,7 @@ wcns_status wcns_batch_rk3_step(wcns_batch_plan* B, double* U, void* work, doubl
     }
     if (!B->cap_stream) WCNS_HIP(hipStreamCreateWithFlags(&B->cap_stream, hipStreamNonBlocking), "stream create");
     WCNS_HIP(hipStreamBeginCapture(B->cap_stream, hipStreamCaptureModeThreadLocal), "begin capture");
-    wcns_status st = batch_step_enqueue(B, U, work, t_dev, t_end, cfl, status_dev, B->cap_stream);
+    wcns_status st = batch_one_step(B, U, work, t_dev, t_end, cfl, status_dev, B->cap_stream);
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(B->cap_stream, &g);
     if (st != WCNS_OK) {
@@ -1281,7 +1373,7 @@ wcns_status wcns_batch_cfl(wcns_batch_plan* B, const double* U, void* work, doub
   SweepArgs a;
   BatchArgs b;
   batch_args(B, (double*)((char*)work + B->off_dtp), &a, &b, work);
-  WCNS_HIP(launch_batch_cfl(U, B->total, b, B->d.gamma, t_dev, t_end, cfl, nullptr, nullptr,
+  WCNS_HIP(launch_batch_cfl(U, B->total, b, B->d.gamma, t_dev, t_dev, t_end, cfl, nullptr, nullptr,
                             (int32_t*)((char*)work + B->off_nlive), (hipStream_t)stream),
            "batch cfl launch");
   return batch_rebuild_live(B, b, work, (hipStream_t)stream);

@@ -129,8 +129,9 @@ hipError_t launch_cfl(int nv, int ndim, const double* U, int64_t npts, double ga
 // *status (when given).  nlive, when given, is cleared for a rebuild of the
 // live list (launch_batch_live) after the kernel.
 hipError_t launch_batch_cfl(const double* U, int64_t total, const BatchArgs& b, double gamma,
-                            double* t, double t_end, double cfl, unsigned long long* wmax,
-                            int32_t* status, int32_t* nlive, hipStream_t stream);
+                            const double* t, double* t_out, double t_end, double cfl,
+                            unsigned long long* wmax, int32_t* status, int32_t* nlive,
+                            hipStream_t stream);
 hipError_t launch_batch_dt(const BatchArgs& b, double* t, double t_end, double cfl,
                            unsigned long long* wmax, int32_t* status, int32_t* nlive,
                            hipStream_t stream);
@@ -171,6 +172,27 @@ struct StageStep {
 bool stage_step_ok(int ndim, int nv, const int64_t n[3]);
 int64_t stage_partials(const int64_t n[3], int diff);
 hipError_t launch_stage_step(int ndim, const StageStep& p, hipStream_t stream);
+// A whole SSP-RK3 step of a small ragged batch in one launch (wcns_pack.hip),
+// bitwise the sweeps' step, from U to another array `out`: tiles of
+// pack_tile_nodes(diff) slots with pack_tile_ghosts(diff) ghosts on each side of
+// a problem, b's tables and count being those tiles'.  s.wmax, where given, gets
+// the maxima of the result (zero before).
+struct PackDt {
+  // dt from the maxima `wmax` of U, the time from t_in to t_out and dt to b.dtp;
+  // wmax null: dt as b.dtp holds it
+  const unsigned long long* wmax;
+  const double* t_in;
+  double* t_out;
+  double t_end, cfl;
+  unsigned long long* clear;  // cleared for the next step's maxima, may be null
+  int32_t* nlive;             // cleared for a rebuild of the live list, may be null
+};
+int64_t pack_max_tiles();
+int pack_tile_nodes(int diff);
+int pack_tile_ghosts(int diff);
+hipError_t launch_pack_step(const SweepArgs& s, const BatchArgs& b, const PackDt& d,
+                            const double* U, double* out,
+                            hipStream_t stream);
 // The filtered embedded WENO sweep of App. B (wcns_weno.hip).
 hipError_t launch_weno_sweep(int nv, int dir, const SweepArgs& a, int mode, hipStream_t stream);
 // Weight histograms of one direction's interpolations (wcns_stats.hip).

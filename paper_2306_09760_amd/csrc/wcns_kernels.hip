@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include "wcns_internal.hpp"
+#include "wcns_sweep_common.hpp"
 
 namespace wcns {
 
@@ -74,35 +75,20 @@ __global__ void __launch_bounds__(256) cfl_final_kernel(const double* __restrict
 }
 
 // The batch maxima use wave_max_bits (wcns_device.hpp).
-// dt_p = min(cfl / m, t_end - t_p) for a problem with t_p < t_end (0
-// otherwise); t_p advances by dt_p.  A maximum rate m that is not positive and
-// finite (a non-finite or non-physical state; NaN bit patterns order above
-// every rate) stops the problem where it is: dt_p = 0, t_p unchanged, bit 0
-// of *status set.
-__device__ __forceinline__ void batch_dt(const BatchArgs& b, int p, double m, double* t,
-                                         double t_end, double cfl, int32_t* status) {
-  const double tp = t[p];
-  if (!(m > 0.0 && m <= 1.79769313486231570815e308)) {
-    b.dtp[p] = 0.0;
-    if (status) atomicOr(status, 1);
-    return;
-  }
-  double dt = cfl / m;
-  double tn = tp + dt;
-  if (!(dt < t_end - tp)) {
-    dt = t_end - tp;
-    tn = t_end;
-  }
-  b.dtp[p] = dt;
-  t[p] = tn;
+__device__ __forceinline__ void batch_dt_store(const BatchArgs& b, int p, const BatchDt& d,
+                                               double* t, int32_t* status) {
+  b.dtp[p] = d.dt;
+  t[p] = d.tn;
+  if (d.bad && status) atomicOr(status, 1);
 }
 
 // One block per problem: the maximum wave rate of its nodes, then batch_dt.
 // wmax, when given, is cleared for the fused maximum of the step's last stage.
+// The time goes from t to t_out (the same array, or another).
 __global__ void __launch_bounds__(256) batch_cfl_kernel(const double* __restrict__ U,
                                                         int64_t total, BatchArgs b,
-                                                        double gamma, double* __restrict__ t,
-                                                        double t_end, double cfl,
+                                                        double gamma, const double* t,
+                                                        double* t_out, double t_end, double cfl,
                                                         unsigned long long* wmax,
                                                         int32_t* status, int32_t* nlive) {
   __shared__ unsigned long long red[4];
@@ -110,13 +96,18 @@ __global__ void __launch_bounds__(256) batch_cfl_kernel(const double* __restrict
   if (nlive && p == 0 && threadIdx.x == 0) *nlive = 0;
   if (wmax && threadIdx.x == 0) wmax[p] = 0;
   if (!(t[p] < t_end)) {  // uniform: the whole block leaves
-    if (threadIdx.x == 0) b.dtp[p] = 0.0;
+    if (threadIdx.x == 0) {
+      b.dtp[p] = 0.0;
+      t_out[p] = t[p];
+    }
     return;
   }
   const int64_t o0 = b.offset[p], o1 = b.offset[p + 1];
   const double ih[1] = {b.ih[p]};
   unsigned long long m = 0;
-  for (int64_t i = o0 + threadIdx.x; i < o1; i += blockDim.x) {
+  // (four nodes' loads in flight: a problem's maximum is a chain of trips to memory)
+#pragma unroll 4
+  for (int64_t i = o0 + threadIdx.x; i < o1; i += 256) {
     double u[3] = {U[i], U[total + i], U[2 * total + i]};
     const unsigned long long r = __builtin_bit_cast(unsigned long long, wave_rate<1>(u, gamma, ih));
     m = r > m ? r : m;
@@ -126,7 +117,7 @@ __global__ void __launch_bounds__(256) batch_cfl_kernel(const double* __restrict
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int w = 1; w < 4; ++w) m = red[w] > m ? red[w] : m;  // m = red[0] here
-    batch_dt(b, p, __builtin_bit_cast(double, m), t, t_end, cfl, status);
+    batch_dt_store(b, p, batch_dt(__builtin_bit_cast(double, m), t[p], t_end, cfl), t_out, status);
   }
 }
 
@@ -142,11 +133,7 @@ __global__ void __launch_bounds__(256) batch_dt_kernel(BatchArgs b, double* __re
   if (p >= b.nprob) return;
   const double m = __builtin_bit_cast(double, wmax[p]);
   wmax[p] = 0;
-  if (!(t[p] < t_end)) {
-    b.dtp[p] = 0.0;
-    return;
-  }
-  batch_dt(b, p, m, t, t_end, cfl, status);
+  batch_dt_store(b, p, batch_dt(m, t[p], t_end, cfl), t, status);
 }
 
 // The live-tile list: lane k tests tile k (live if one of its problems has
@@ -227,10 +214,11 @@ hipError_t launch_cfl(int nv, int ndim, const double* U, int64_t npts, double ga
 }
 
 hipError_t launch_batch_cfl(const double* U, int64_t total, const BatchArgs& b, double gamma,
-                            double* t, double t_end, double cfl, unsigned long long* wmax,
-                            int32_t* status, int32_t* nlive, hipStream_t stream) {
+                            const double* t, double* t_out, double t_end, double cfl,
+                            unsigned long long* wmax, int32_t* status, int32_t* nlive,
+                            hipStream_t stream) {
   hipLaunchKernelGGL(batch_cfl_kernel, dim3(b.nprob), dim3(256), 0, stream, U, total, b, gamma,
-                     t, t_end, cfl, wmax, status, nlive);
+                     t, t_out, t_end, cfl, wmax, status, nlive);
   return hipGetLastError();
 }
 

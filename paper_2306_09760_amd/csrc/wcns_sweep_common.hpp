@@ -173,6 +173,51 @@ __device__ __forceinline__ void flag_status(int32_t* status) {
   if (status) atomicOr(status, 1);
 }
 
+// U^(k+1) = ca U0 + cb (U^k + dt R), as emit's stage combine rounds it.
+__device__ __forceinline__ double stage_value(double ca, double cb, double u0, double uk, double dt,
+                                              double r) {
+  return __builtin_fma(ca, u0, cb * __builtin_fma(dt, r, uk));
+}
+
+// A problem's step of the batch: dt = min(cfl / m, t_end - t) with t advanced to
+// tn, for a problem with t < t_end (dt = 0 otherwise).  A maximum rate m that is
+// not positive and finite (a non-finite or non-physical state; NaN bit patterns
+// order above every rate) stops the problem where it is: dt = 0, t kept, bad.
+struct BatchDt {
+  double dt, tn;
+  bool bad;
+};
+__device__ __forceinline__ BatchDt batch_dt(double m, double t, double t_end, double cfl) {
+  if (!(t < t_end)) return {0.0, t, false};
+  if (!(m > 0.0 && m <= 1.79769313486231570815e308)) return {0.0, t, true};
+  const double dt = cfl / m;
+  if (!(dt < t_end - t)) return {t_end - t, t_end, false};
+  return {dt, t + dt, false};
+}
+
+// The maxima of the lanes' wave rates (bit patterns, 0: none) into their
+// problems' entries; all lanes of the wavefront call it.
+__device__ __forceinline__ void batch_rate_max(unsigned long long* wmax, const BatchTile& bt,
+                                               bool near, int prob, unsigned long long rbits) {
+  if (near) {
+    // The lanes' nodes belong to p0 or p0 + 1, in order, so at most one
+    // wavefront of the tile holds both: reduce only for the problems a
+    // wavefront holds (the ballots are uniform across it).
+    const bool first = (threadIdx.x & 63) == 0;
+    const bool s1 = prob != bt.p0;
+    if (__ballot(rbits != 0 && !s1)) {
+      const unsigned long long m0 = wave_max_bits(s1 ? 0ull : rbits);
+      if (first) atomicMax(wmax + bt.p0, m0);
+    }
+    if (__ballot(rbits != 0 && s1)) {
+      const unsigned long long m1 = wave_max_bits(s1 ? rbits : 0ull);
+      if (first) atomicMax(wmax + bt.p0 + 1, m1);
+    }
+  } else if (rbits) {
+    atomicMax(wmax + prob, rbits);
+  }
+}
+
 // The fields of SweepArgs that writing a result needs (emit): a kernel may
 // read them late, from its argument segment, instead of holding them in
 // scalar registers through its main loop.

@@ -163,12 +163,6 @@ __device__ __forceinline__ T& at_bytes(T* p, uint32_t off) {
   return *reinterpret_cast<T*>(reinterpret_cast<C*>(p) + off);
 }
 
-// U^(k+1) = ca U0 + cb (U^k + dt R), as emit's stage combine rounds it.
-__device__ __forceinline__ double stage_value(double ca, double cb, double u0, double uk, double dt,
-                                              double r) {
-  return __builtin_fma(ca, u0, cb * __builtin_fma(dt, r, uk));
-}
-
 // One tile (logical index `tile`) of a sweep; every lane of the workgroup
 // calls it from sweep_kernel (its late phases re-read the kernel arguments).
 // STEP: a tile of a one-launch stage, with its state from StageIn and its
@@ -630,22 +624,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
   // rate of the state it writes (uniform branch; every lane reaches it).
   if constexpr (BATCH) {
     if (a.wmax && mode == MODE_STAGE) {
-      if (near) {
-        // The lanes' nodes belong to p0 or p0 + 1, in order, so at most one
-        // wavefront of the tile holds both: reduce only for the problems a
-        // wavefront holds (the ballots are uniform across it).
-        const bool s1 = oprob != bt.p0;
-        if (__ballot(rbits != 0 && !s1)) {
-          const unsigned long long m0 = wave_max_bits(s1 ? 0ull : rbits);
-          if ((tid & 63) == 0) atomicMax(a.wmax + bt.p0, m0);
-        }
-        if (__ballot(rbits != 0 && s1)) {
-          const unsigned long long m1 = wave_max_bits(s1 ? rbits : 0ull);
-          if ((tid & 63) == 0) atomicMax(a.wmax + bt.p0 + 1, m1);
-        }
-      } else if (rbits) {
-        atomicMax(a.wmax + oprob, rbits);
-      }
+      batch_rate_max(a.wmax, bt, near, oprob, rbits);
     }
   }
 }
