@@ -53,18 +53,32 @@ namespace wcns {
 // three), the 4-variable one 25 KB instead of 35 KB.
 constexpr bool sweep_reg(int nv, int tmw) { return tmw == 256 && nv > 1 && nv >= WCNS_REG_MIN_NV; }
 
+// The 5-variable y and z tiles of four and eight columns keep the last field's
+// two states in registers between the interpolation and the flux, and the node
+// fluxes of their last two variables in the tile's own nodes, which nobody reads
+// by then (one more barrier): two rows of sW less let a CU's LDS hold five of
+// them instead of four (a 32 x 8 tile 28.7 instead of 32.8 KB; the 64 x 4 one of
+// 32.0 KB, too, took the room of four).  Residual 256^3, Z 2.300 -> 2.219 ms, FE
+// 3.135 -> 3.105; 200 x 190 x 180, FE 1.375 -> 1.350.
+constexpr bool sweep_trim(int nv, int tm, int w) {
+  return nv == 5 && sweep_reg(nv, tm * w) && w >= 4;
+}
+
 // LDS doubles of a tile: nodes sU[NV][TM+5][W] | Roe states sR[NR][TM W]
 // (none on the register path) | interpolated states sW[2 NV][TM W] | the
 // 64-entry exp table.
 constexpr size_t sweep_lds_doubles(int nv, int tm, int w) {
   const size_t nr = (nv > 1 && !sweep_reg(nv, tm * w)) ? (size_t)nv + 1 : 0;
-  return (size_t)nv * (tm + 5) * w + (nr + 2 * (size_t)nv) * ((size_t)tm * w) + 64;
+  const size_t rows = nr + 2 * (size_t)nv - (sweep_trim(nv, tm, w) ? 2 : 0);
+  return (size_t)nv * (tm + 5) * w + rows * ((size_t)tm * w) + 64;
 }
 
 template <int NV, int TM, int W>
 struct SweepLayout {
   static constexpr int ND = NV > 1 ? NV - 2 : 1;
   static constexpr bool REG = sweep_reg(NV, TM * W);
+  static constexpr bool TRIM = sweep_trim(NV, TM, W);
+  static constexpr int NS = 2 * NV - (TRIM ? 2 : 0);   // rows of sW
   static constexpr int NR = (NV > 1 && !REG) ? NV - 2 + 3 : 0;  // vel[ND], H, c, ic
   static constexpr int TN = TM + 5;                    // nodes per column
   static constexpr int TMW = TM * W;                   // midpoints per tile
@@ -72,7 +86,7 @@ struct SweepLayout {
   static constexpr int LW = W == 1 ? 0 : W == 2 ? 1 : W == 4 ? 2 : W == 8 ? 3 : 4;
   static constexpr int LTMW = TMW == 128 ? 7 : 8;
   static constexpr size_t lds_doubles = sweep_lds_doubles(NV, TM, W);
-  static_assert(lds_doubles == (size_t)NV * SV + (size_t)(NR + 2 * NV) * TMW + 64, "LDS layout");
+  static_assert(lds_doubles == (size_t)NV * SV + (size_t)(NR + NS) * TMW + 64, "LDS layout");
   static_assert(TMW == 128 || TMW == 256, "tile must hold 128 or 256 midpoints");
   static_assert((1 << LW) == W, "W must be a power of two up to 16");
 };
@@ -180,7 +194,9 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
   double* sU = smem;
   double* sR = sU + NV * SV;
   double* sW = sR + NR * TMW;
-  double* sX = sW + 2 * NV * TMW;  // exp2_tab_entry
+  double* sX = sW + L::NS * TMW;  // exp2_tab_entry
+  constexpr bool TRIM = L::TRIM;
+  constexpr int RO = TRIM ? NV - 1 : NV;  // the right states' first row of sW
   const int tid = threadIdx.x;
   const int G = a.diff ? 5 : 4;
   const int TL = TM - (a.diff ? 5 : 3);
@@ -399,6 +415,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
     }
   }
 
+  double wl = 0.0, wr = 0.0;  // TRIM: the last field's states
   // one field of one midpoint per task: its left- and right-biased
   // interpolations share the six projected stencil values
 #pragma unroll 1
@@ -452,7 +469,15 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
 #pragma unroll
       for (int j = 0; j < 6; ++j) w[j] = uv[j * W];
     }
-    interp5_pair<SPEC>(a.ip, w, sW + q, sW + NV * TMW + q, sX);
+    if constexpr (TRIM) {
+      interp5_pair<SPEC>(a.ip, w, &wl, &wr, sX);
+      if (v < NV - 1) {
+        sW[q] = wl;
+        sW[RO * TMW + q] = wr;
+      }
+    } else {
+      interp5_pair<SPEC>(a.ip, w, sW + q, sW + NV * TMW + q, sX);
+    }
   }
   if constexpr (!OWN) __syncthreads();
 
@@ -469,6 +494,15 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
     }
   }
 
+  // TRIM: the lane's output node's last two variables, and the node fluxes of
+  // those on their way into sU
+  double Ut[2] = {}, Ft[2] = {};
+  if constexpr (TRIM) {
+    if (tid < TL * W) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) Ut[t] = sU[(NV - 2 + t) * SV + tid + G * W];
+    }
+  }
   // midpoint flux (overwrites sW rows 0..NV-1 of the same midpoint)
 #pragma unroll 1
   for (int q = tid; q < TMW; q += NT) {
@@ -481,8 +515,8 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
       double WL[NV], WR[NV], UL[NV], UR[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        WL[v] = sW[v * TMW + q];
-        WR[v] = sW[(NV + v) * TMW + q];
+        WL[v] = TRIM && v == NV - 1 ? wl : sW[v * TMW + q];
+        WR[v] = TRIM && v == NV - 1 ? wr : sW[(RO + v) * TMW + q];
       }
       if (proj) {
         RoeState<ND> rs = rsq;
@@ -517,7 +551,19 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
       for (int v = 0; v < NV; ++v) Uc[v] = sU[v * SV + q + 2 * W];
       node_flux<NV, DIR>(a.pp, Uc, Fc);
 #pragma unroll
-      for (int v = 0; v < NV; ++v) sW[(NV + v) * TMW + q] = Fc[v];
+      for (int v = 0; v < NV; ++v) {
+        if (TRIM && v >= NV - 2)
+          Ft[v - (NV - 2)] = Fc[v];
+        else
+          sW[(NV + v) * TMW + q] = Fc[v];
+      }
+    }
+  }
+  if constexpr (TRIM) {
+    if (a.diff == 0) {
+      __syncthreads();  // the last reads of sU
+#pragma unroll
+      for (int t = 0; t < 2; ++t) sU[(NV - 2 + t) * SV + tid + 2 * W] = Ft[t];
     }
   }
   __syncthreads();
@@ -561,10 +607,11 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
     if (a.diff == 0) {
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        Un[v] = u[v * SV + 4 * W];
+        const bool tv = TRIM && v >= NV - 2;
+        Un[v] = tv ? Ut[v - (NV - 2)] : u[v * SV + 4 * W];
         const lds_cptr fv = lds_row(f + v * TMW);
         // F of node t + k + 2 at nf[k W]: nodes t + 3 and t + 5 around t + 4
-        const lds_cptr nf = lds_row(f + (NV + v) * TMW);
+        const lds_cptr nf = lds_row(tv ? u + v * SV + 2 * W : f + (NV + v) * TMW);
         const double d = __builtin_fma(
             0.75, fv[2 * W] - fv[W],
             __builtin_fma(-0.3, nf[3 * W] - nf[W], (1.0 / 60.0) * (fv[3 * W] - fv[0])));
@@ -634,7 +681,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
 // midpoints, 27.3 KB of LDS) still fits six workgroups in a CU's 160 KB.
 // The register path runs at five (at most 102 VGPRs; 86-90 used, no spills):
 // at six its Roe state spills, and LDS allows five 5-variable tiles per CU
-// (four for the 32 x 8 tile) against three before.
+// against three before.
 // The generic interpolation needs ~110 VGPRs and is left unconstrained
 // (capped at 80 it spills); the saturating FE one (SPEC_FE_SAT) needs ~118
 // and runs at four.
