@@ -402,6 +402,14 @@ __device__ __forceinline__ double fe_map_poly(double w, double X, const double* 
 struct FamWcns {
   static constexpr double scale = 0.125;
   static constexpr double dr1 = 10.0, dr2 = 5.0;  // d_1 / d_0, d_2 / d_0
+  static constexpr double d0 = D0, d1 = D1, d2 = D2;
+  // the maps' A_j
+  static constexpr const double (&g0a())[3] { return kG0a; }
+  static constexpr const double (&g0b())[3] { return kG0b; }
+  static constexpr const double (&g1a())[4] { return kG1a; }
+  static constexpr const double (&g1b())[4] { return kG1b; }
+  static constexpr const double (&g2a())[3] { return kG2a; }
+  static constexpr const double (&g2b())[3] { return kG2b; }
 };
 
 // um plus FAM::scale times the mean of x0, x1, x2 under the FE images of the
@@ -479,8 +487,8 @@ __device__ __forceinline__ double fe_stair(double w, const double (&a)[NT], cons
 // stencil's middle node, divided by FAM::scale (which is applied once, to the
 // sum): the weights sum to one, so the result is um plus the weighted mean
 // distance, the weights' rounding errors multiply distances instead of
-// values, and a flat stencil returns um itself.  The FE branch serves either
-// family (FAM); the others are the WCNS one.
+// values, and a flat stencil returns um itself.  The specialised branches serve
+// either family (FAM); the run-time one is the WCNS one.
 // Bound by FP64 VALU issue: one task of two interpolations takes 219 VALU
 // instructions in the batch kernel (195 of them FP64), 266 with the Z weights
 // as sums times products, a reciprocal for the third map's variable, a
@@ -514,38 +522,41 @@ __device__ __forceinline__ double weigh5(const InterpParams& P, double um, doubl
     const double zi = rcp(z0 + z1 + z2);
     const double w0 = z0 * zi, w1 = z1 * zi, w2 = z2 * zi;
     if constexpr (SPEC == SPEC_FE) return fe_mean<FAM>(P, w0, w1, w2, um, x0, x1, x2, xt);
+    if (P.weights == WPFE && __builtin_fabs(w0 - FAM::d0) <= P.cv &&
+        __builtin_fabs(w1 - FAM::d1) <= P.cv && __builtin_fabs(w2 - FAM::d2) <= P.cv)
+      return __builtin_fma(FAM::scale, __builtin_fma(w0, x0, __builtin_fma(w1, x1, w2 * x2)), um);
     // Each map is a staircase (exactly: no rounding of the sum of its terms);
     // a lane near a null point takes the terms themselves.
-    const double g0 = fe_stair<3>(w0, kG0a, kG0b, P.K, P, xt);
-    const double g1 = fe_stair<4>(w1, kG1a, kG1b, P.K + 3, P, xt);
-    const double g2 = fe_stair<3>(w2, kG2a, kG2b, P.K + 7, P, xt);
+    const double g0 = fe_stair<3>(w0, FAM::g0a(), FAM::g0b(), P.K, P, xt);
+    const double g1 = fe_stair<4>(w1, FAM::g1a(), FAM::g1b(), P.K + 3, P, xt);
+    const double g2 = fe_stair<3>(w2, FAM::g2a(), FAM::g2b(), P.K + 7, P, xt);
     const double ginv = rcp(g0 + g1 + g2);
-    return __builtin_fma(0.125 * ginv, __builtin_fma(g0, x0, __builtin_fma(g1, x1, g2 * x2)), um);
+    return __builtin_fma(FAM::scale * ginv, __builtin_fma(g0, x0, __builtin_fma(g1, x1, g2 * x2)), um);
   }
   if constexpr (SPEC == SPEC_JS) {
     // alpha_k = d_k / b_k^2 times b_0^2 b_1^2 b_2^2: no reciprocal but the sum's
     const double m0 = b1 * b2, m1 = b0 * b2, m2 = b0 * b1;
-    const double z0 = m0 * m0, z1 = 10.0 * (m1 * m1), z2 = 5.0 * (m2 * m2);
+    const double z0 = m0 * m0, z1 = FAM::dr1 * (m1 * m1), z2 = FAM::dr2 * (m2 * m2);
     const double zi = rcp(z0 + z1 + z2);
     const double num = __builtin_fma(z0, x0, __builtin_fma(z1, x1, z2 * x2));
-    return __builtin_fma(0.125 * num, zi, um);
+    return __builtin_fma(FAM::scale * num, zi, um);
   }
   if constexpr (SPEC == SPEC_Z || SPEC == SPEC_PFE) {
     // alpha_k = d_k (1 + (tau / b_k)^2) with one reciprocal for the three 1 / b_k
     const double m0 = b1 * b2, m1 = b0 * b2, m2 = b0 * b1;
     const double tr = (b0 - b2) * rcp(b0 * m0);
     const double a0 = tr * m0, a1 = tr * m1, a2 = tr * m2;
-    const double z0 = __builtin_fma(a0, a0, 1.0), z1 = 10.0 * __builtin_fma(a1, a1, 1.0),
-                 z2 = 5.0 * __builtin_fma(a2, a2, 1.0);
+    const double z0 = __builtin_fma(a0, a0, 1.0), z1 = FAM::dr1 * __builtin_fma(a1, a1, 1.0),
+                 z2 = FAM::dr2 * __builtin_fma(a2, a2, 1.0);
     const double zi = rcp(z0 + z1 + z2);
     if constexpr (SPEC == SPEC_Z) {
       const double num = __builtin_fma(z0, x0, __builtin_fma(z1, x1, z2 * x2));
-      return __builtin_fma(0.125 * num, zi, um);
+      return __builtin_fma(FAM::scale * num, zi, um);
     }
     const double w0 = z0 * zi, w1 = z1 * zi, w2 = z2 * zi;
-    if (__builtin_fabs(w0 - D0) <= P.cv && __builtin_fabs(w1 - D1) <= P.cv &&
-        __builtin_fabs(w2 - D2) <= P.cv)
-      return __builtin_fma(0.125, __builtin_fma(w0, x0, __builtin_fma(w1, x1, w2 * x2)), um);
+    if (__builtin_fabs(w0 - FAM::d0) <= P.cv && __builtin_fabs(w1 - FAM::d1) <= P.cv &&
+        __builtin_fabs(w2 - FAM::d2) <= P.cv)
+      return __builtin_fma(FAM::scale, __builtin_fma(w0, x0, __builtin_fma(w1, x1, w2 * x2)), um);
     return fe_mean<FAM>(P, w0, w1, w2, um, x0, x1, x2, xt);
   }
   double a0, a1, a2;
@@ -648,24 +659,31 @@ static_assert(map_sums_vanish(kV0a, kV0b, 3) && map_sums_vanish(kV1a, kV1b, 4) &
 struct FamWeno {
   static constexpr double scale = 1.0 / 12.0;
   static constexpr double dr1 = 6.0, dr2 = 3.0;  // d_1 / d_0, d_2 / d_0
+  static constexpr double d0 = E0, d1 = E1, d2 = E2;
+  static constexpr const double (&g0a())[3] { return kV0a; }
+  static constexpr const double (&g0b())[3] { return kV0b; }
+  static constexpr const double (&g1a())[4] { return kV1a; }
+  static constexpr const double (&g1b())[4] { return kV1b; }
+  static constexpr const double (&g2a())[3] { return kV2a; }
+  static constexpr const double (&g2b())[3] { return kV2b; }
 };
 
-// weno5 with FE weights on p = 2 Z weights through the fast path of weigh5
-// (Table B.1 ideal weights, Table B.2 maps); xt: the exp2_tab_entry table in
-// LDS.  With f_k and s_k as in interp5_pair, B_k = f_k^2 + 13/12 s_k^2 and
+// weno5 through the specialised paths of weigh5 (Table B.1 ideal weights, Table
+// B.2 maps); xt: the exp2_tab_entry table in LDS.  With f_k and s_k as in interp5_pair, B_k = f_k^2 + 13/12 s_k^2 and
 // the candidate is c + f_k / 2 + s_k / 12.  eps: added to the B_k.
-__device__ __forceinline__ double weno5_fe(const InterpParams& P, double eps, double a, double b,
-                                           double c, double e, double f, const double* xt) {
+template <int SPEC>
+__device__ __forceinline__ double weno5_spec(const InterpParams& P, double eps, double a, double b,
+                                             double c, double e, double f, const double* xt) {
   constexpr double k = 13.0 / 12.0;
   const double d0 = b - a, d1 = c - b, d2 = e - c, d3 = f - e;
   const double s0 = d1 - d0, s1 = d2 - d1, s2 = d3 - d2;
   const double f0 = __builtin_fma(0.5, s0, d1), f1 = __builtin_fma(0.5, s1, d1),
                f2 = __builtin_fma(-0.5, s2, d2);
-  return weigh5<SPEC_FE, FamWeno>(P, c, __builtin_fma(6.0, f0, s0), __builtin_fma(6.0, f1, s1),
-                                  __builtin_fma(6.0, f2, s2),
-                                  __builtin_fma(f0, f0, __builtin_fma(k * s0, s0, eps)),
-                                  __builtin_fma(f1, f1, __builtin_fma(k * s1, s1, eps)),
-                                  __builtin_fma(f2, f2, __builtin_fma(k * s2, s2, eps)), xt);
+  return weigh5<SPEC, FamWeno>(P, c, __builtin_fma(6.0, f0, s0), __builtin_fma(6.0, f1, s1),
+                               __builtin_fma(6.0, f2, s2),
+                               __builtin_fma(f0, f0, __builtin_fma(k * s0, s0, eps)),
+                               __builtin_fma(f1, f1, __builtin_fma(k * s1, s1, eps)),
+                               __builtin_fma(f2, f2, __builtin_fma(k * s2, s2, eps)), xt);
 }
 
 // Finite-difference WENO5 reconstruction at x_{i+1/2} from the point values

@@ -2,8 +2,9 @@
 // finite-difference WENO5 with Lax-Friedrichs flux splitting and a
 // conservative difference, on the tiles of the WCNS sweep.
 //
-// A workgroup of 128 lanes owns TM midpoints (TM W = 128) of W adjacent columns,
-// one midpoint per lane, and writes the TL = TM - 1 nodes between them.
+// A workgroup of 128 GR lanes owns TM midpoints (TM W = 128) of W adjacent columns,
+// one midpoint per lane (GR = 2, for small grids: two lanes per midpoint, every
+// other field each), and writes the TL = TM - 1 nodes between them.
 // Along x the lines are packed end to end (TileGeom::lines, 3 ghost slots per
 // side).  Phases:
 //   load     the TM+5 nodes of every column, ghosts applied; each lane takes
@@ -26,8 +27,12 @@
 // five phases: residual 2D 512^2 0.0598 -> 0.0445 ms, 1024^2 0.179 -> 0.127,
 // 2048^2 0.635 -> 0.436, 3D 128^3 0.892 -> 0.497 ms.  256 lanes on 256
 // midpoints are 1 % faster from 1024^2 on, and 13 % slower in 3D.
+// The weights have the kernels of the WCNS sweep (spec_of): with the run-time ones
+// for all but FE, residual 2D 1000 x 993 PFE 0.161 -> 0.101 ms, Z 0.153 -> 0.093, JS
+// 0.148 -> 0.088, FE at xi = 1e6 0.187 -> 0.116; 3D 64^3 PFE 0.222 -> 0.103 ms (each
+// against the five phases).
 // LDS (doubles): sU[NV][TM+5][W] | sF[NV-1][TM+5][W] | sL[TM+5][W] |
-// sW[NV][128] | the exp table (FE specialisation).
+// sW[NV][128] | the exp table.
 #include <hip/hip_runtime.h>
 
 #include "wcns_internal.hpp"
@@ -47,16 +52,16 @@ struct WenoLayout {
   static_assert(TMW == 128, "one midpoint per lane");
 };
 
-// Register budget: the FE specialisation fits five waves per SIMD, the
-// run-time weights four.
-constexpr int weno_waves(int spec) { return spec == SPEC_FE ? 5 : 4; }
+// Register budget: the specialisations fit five waves per SIMD, the staircase maps
+// four, the run-time weights three (at four they spill).
+constexpr int weno_waves(int spec) { return spec == SPEC_GENERIC ? 3 : spec == SPEC_FE_SAT ? 4 : 5; }
 
-template <int NV, int DIR, int SPEC, int TM, int W>
-__global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(weno_waves(SPEC))))
+template <int NV, int DIR, int SPEC, int TM, int W, int GR>
+__global__ void __launch_bounds__(128 * GR) __attribute__((amdgpu_waves_per_eu(weno_waves(SPEC))))
     weno_sweep_kernel(SweepArgs a, TileGeom g, int mode) {
   using L = WenoLayout<NV, TM, W>;
   constexpr int ND = L::ND, TMW = L::TMW, SV = L::SV, LW = L::LW;
-  constexpr int NT = TMW;
+  constexpr int NT = TMW * GR;
   constexpr int TL = TM - 1;
   constexpr int G = 3;  // ghosts on each side
   extern __shared__ double smem[];
@@ -66,6 +71,8 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(weno_w
   double* sW = NV > 1 ? sL + SV : sU + SV;
   double* sX = sW + NV * TMW;  // exp2_tab_entry
   const int tid = threadIdx.x;
+  const int mid = tid & (TMW - 1);                                    // the lane's midpoint
+  const int grp = GR > 1 ? __builtin_amdgcn_readfirstlane(tid >> 7) : 0;  // and its fields'
 
   if ((int64_t)blockIdx.x >= g.ntiles) return;
   const int64_t tile = xcd_tile(blockIdx.x, g.ntiles);
@@ -136,7 +143,7 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(weno_w
       if (sl.j >= 0 && sl.j < sl.n) onode = sl.o + sl.j;
     }
   }
-  if constexpr (SPEC == SPEC_FE) {
+  if constexpr (spec_table(SPEC)) {
     if (tid < 64) sX[tid] = exp2_tab_entry(tid, a.ip.xsh);
   }
 #pragma unroll
@@ -164,11 +171,11 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(weno_w
   RoeState<ND> rsq{};
   double al = 0.0;
   if constexpr (NV > 1) {
-    al = sL[tid];
+    al = sL[mid];
 #pragma unroll
-    for (int j = 1; j < 6; ++j) al = __builtin_fmax(al, sL[tid + j * W]);
+    for (int j = 1; j < 6; ++j) al = __builtin_fmax(al, sL[mid + j * W]);
     if (proj) {
-      const double* u = sU + tid + 2 * W;
+      const double* u = sU + mid + 2 * W;
       double UA[NV], UB[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
@@ -181,21 +188,21 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(weno_w
 
   // reconstruction of each field at the lane's midpoint
 #pragma unroll 1
-  for (int v = 0; v < NV; ++v) {
+  for (int v = grp; v < NV; v += GR) {
     double wp[5], wm[5];  // F + alpha U of nodes 0 .. 4, F - alpha U of nodes 5 .. 1
     if constexpr (NV == 1) {
       const double sp = a.pp.adv + __builtin_fabs(a.pp.adv);
       const double sm = a.pp.adv - __builtin_fabs(a.pp.adv);
 #pragma unroll
       for (int j = 0; j < 5; ++j) {
-        wp[j] = sp * sU[tid + j * W];
-        wm[j] = sm * sU[tid + (5 - j) * W];
+        wp[j] = sp * sU[mid + j * W];
+        wm[j] = sm * sU[mid + (5 - j) * W];
       }
     } else {
       double wu[6], wf[6];
-      const double* u = sU + tid;
-      const double* fr = sU + (1 + DIR) * SV + tid;  // the density's flux
-      const double* f = sF + tid;                    // row e - 1: component e
+      const double* u = sU + mid;
+      const double* fr = sU + (1 + DIR) * SV + mid;  // the density's flux
+      const double* f = sF + mid;                    // row e - 1: component e
       if (proj) {
         if (v >= 2 && v < NV - 1) {  // shear field: X_ax - vel_ax X_rho
           const int ax = tangential_axis<ND, DIR>(v - 2);
@@ -246,24 +253,25 @@ __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(weno_w
       }
     }
     double r;
-    if constexpr (SPEC == SPEC_FE)
-      r = weno5_fe(a.ip, eps4, wp[0], wp[1], wp[2], wp[3], wp[4], sX) +
-          weno5_fe(a.ip, eps4, wm[0], wm[1], wm[2], wm[3], wm[4], sX);
+    if constexpr (SPEC != SPEC_GENERIC)
+      r = weno5_spec<SPEC>(a.ip, eps4, wp[0], wp[1], wp[2], wp[3], wp[4], sX) +
+          weno5_spec<SPEC>(a.ip, eps4, wm[0], wm[1], wm[2], wm[3], wm[4], sX);
     else
       r = weno5(a.ip, eps4, wp[0], wp[1], wp[2], wp[3], wp[4]) +
           weno5(a.ip, eps4, wm[0], wm[1], wm[2], wm[3], wm[4]);
-    sW[v * TMW + tid] = r;
+    sW[v * TMW + mid] = r;
   }
 
   // twice the midpoint flux, 2 F~ = R (f+^ + f-^), of the lane's own midpoint
+  if constexpr (GR > 1) __syncthreads();
   if constexpr (NV > 1) {
-    if (proj) {
+    if (proj && grp == 0) {
       double Gv[NV], F[NV];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) Gv[v] = sW[v * TMW + tid];
+      for (int v = 0; v < NV; ++v) Gv[v] = sW[v * TMW + mid];
       unproject<ND, DIR>(rsq, Gv, F);
 #pragma unroll
-      for (int v = 0; v < NV; ++v) sW[v * TMW + tid] = F[v];
+      for (int v = 0; v < NV; ++v) sW[v * TMW + mid] = F[v];
     }
   }
   __syncthreads();
@@ -315,12 +323,27 @@ static hipError_t weno_go(const SweepArgs& a, int mode, hipStream_t s) {
     g.ntiles = (others * len + g.tl - 1) / g.tl;
   }
   if (g.ntiles > 0x7fffffff) return hipErrorInvalidConfiguration;
-  if (spec_of(a.ip) == SPEC_FE)
-    hipLaunchKernelGGL((weno_sweep_kernel<NV, DIR, SPEC_FE, TM, W>), dim3((unsigned)g.ntiles),
-                       dim3(L::TMW), sizeof(double) * L::lds_doubles, s, a, g, mode);
-  else
-    hipLaunchKernelGGL((weno_sweep_kernel<NV, DIR, SPEC_GENERIC, TM, W>), dim3((unsigned)g.ntiles),
-                       dim3(L::TMW), sizeof(double) * L::lds_doubles, s, a, g, mode);
+  // Two lanes per midpoint while a CU has five or six tiles at most: such a sweep is
+  // the length of one tile's chain of fields.  One lane -> two, residuals: 2D 60 x 53
+  // FE 17.2 -> 14.9 us, PFE 18.7 -> 14.4, 400 x 393 FE 33.9 -> 31.0, JS 24.3 -> 23.5
+  // (1300 tiles); 460^2 (1700) FE 39.2 -> 38.4, JS 26.4 -> 27.3; 1000^2 FE 127 -> 134.
+  const bool split = NV > 1 && g.ntiles <= 1408;
+#define WCNS_W(SP)                                                                              \
+  case SP:                                                                                      \
+    if (split)                                                                                  \
+      hipLaunchKernelGGL((weno_sweep_kernel<NV, DIR, SP, TM, W, NV == 1 ? 1 : 2>),              \
+                         dim3((unsigned)g.ntiles), dim3(2 * L::TMW),                            \
+                         sizeof(double) * L::lds_doubles, s, a, g, mode);                       \
+    else                                                                                        \
+      hipLaunchKernelGGL((weno_sweep_kernel<NV, DIR, SP, TM, W, 1>), dim3((unsigned)g.ntiles),  \
+                         dim3(L::TMW), sizeof(double) * L::lds_doubles, s, a, g, mode);         \
+    break;
+  switch (spec_of(a.ip)) {
+    WCNS_W(SPEC_FE) WCNS_W(SPEC_FE_SAT) WCNS_W(SPEC_JS) WCNS_W(SPEC_Z) WCNS_W(SPEC_PFE)
+    default:
+    WCNS_W(SPEC_GENERIC)
+  }
+#undef WCNS_W
   return hipGetLastError();
 }
 
