@@ -748,8 +748,7 @@ wcns_status wcns_rk4_step(wcns_plan* plan, double* U, void* work, const double* 
   if ((st = stage_lin(plan, U1, U, U2, 1.0, 0.0, 0.5, dt, Racc, status_dev, s)) != WCNS_OK) return st;
   if ((st = stage_lin(plan, U2, U, U3, 1.0, 0.0, 1.0, dt, Racc, status_dev, s)) != WCNS_OK) return st;
   // u_new = (-u + u1 + 2 u2)/3 + u3/3 + dt/6 L(u3)
-  WCNS_HIP(launch_lincomb(A, U, -1.0 / 3.0, U1, 1.0 / 3.0, nullptr, 0.0, len, s), "lincomb");
-  WCNS_HIP(launch_axpy_state(A, U2, 2.0 / 3.0, len, s), "axpy");
+  WCNS_HIP(launch_rk4_sum(A, U, U1, U2, len, s), "stage sum");
   return stage_lin(plan, U3, A, U, 1.0, 1.0 / 3.0, 1.0 / 6.0, dt, Racc, status_dev, s);
 }
 

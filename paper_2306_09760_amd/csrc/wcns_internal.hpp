@@ -145,8 +145,8 @@ hipError_t launch_batch_dt(const BatchArgs& b, double* t, double t_end, double c
 // live[] in runs of consecutive tiles (nlive must be 0 before).
 hipError_t launch_batch_live(const BatchArgs& b, int32_t* live, int32_t* nlive,
                              hipStream_t stream);
-hipError_t launch_axpy_state(double* y, const double* x, double a, int64_t n,
-                             hipStream_t stream);
+hipError_t launch_rk4_sum(double* out, const double* u, const double* u1, const double* u2,
+                          int64_t n, hipStream_t stream);
 hipError_t launch_lincomb(double* out, const double* x, double ax, const double* y, double ay,
                           const double* dt, double ydt, int64_t n, hipStream_t stream);
 // A whole step of a short 1D WCNS problem in one launch (wcns_line.hip), bitwise

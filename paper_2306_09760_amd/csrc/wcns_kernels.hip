@@ -1,9 +1,9 @@
 // Time-step and elementwise kernels of the WCNS-FE library on gfx950 (the
 // directional sweeps are in wcns_sweep.hip).
 //
-//  cfl      two deterministic passes: per-block maxima of
-//           sum_d (|u_d| + c)/h_d (wavefront shuffles, then LDS), then one
-//           block that turns the maximum into dt = cfl / max.
+//  cfl      sum_d (|u_d| + c)/h_d, its maximum and dt = cfl / max: one block for
+//           a small grid, else per-block maxima and one block that turns them
+//           into dt (both deterministic).
 #include <hip/hip_runtime.h>
 
 #include "wcns_internal.hpp"
@@ -12,66 +12,62 @@
 namespace wcns {
 
 // --------------------------------------------------------------------- CFL --
-__device__ __forceinline__ double wave_max(double v) {
+// Maximum of a block of WAVES wavefronts; valid in every thread (bit patterns:
+// a NaN reaches dt from any lane, see wave_max_bits).
+template <int WAVES>
+__device__ __forceinline__ unsigned long long block_max_bits(unsigned long long m) {
+  __shared__ unsigned long long red[WAVES];
+  m = wave_max_bits(m);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  m = red[0];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const double w = __shfl_xor(v, o, 64);
-    v = (w > v) ? w : v;
-  }
-  return v;
+  for (int w = 1; w < WAVES; ++w) m = umax64(m, red[w]);
+  return m;
 }
 
-// Block maximum for blockDim.x == 256; result valid in thread 0.
-__device__ __forceinline__ double block_max256(double v) {
-  __shared__ double red[4];
-  v = wave_max(v);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) red[w] = v;
-  __syncthreads();
-  double r = red[0];
-  r = red[1] > r ? red[1] : r;
-  r = red[2] > r ? red[2] : r;
-  r = red[3] > r ? red[3] : r;
-  __syncthreads();
-  return r;
-}
-
+// Maximum wave rate over the nodes first, first + step, ..
 template <int NV>
-__global__ void __launch_bounds__(256) cfl_partial_kernel(const double* __restrict__ U,
-                                                          int64_t npts, double gamma,
-                                                          double ih0, double ih1, double ih2,
-                                                          double adv_rate,
-                                                          double* __restrict__ partial) {
-  double m = 0.0;
+__device__ __forceinline__ unsigned long long rate_max(const double* __restrict__ U, int64_t npts,
+                                                       double gamma, const double (&ih)[3],
+                                                       double adv_rate, int64_t first, int64_t step) {
+  unsigned long long m = 0;
   if constexpr (NV == 1) {
-    m = adv_rate;
+    m = __builtin_bit_cast(unsigned long long, adv_rate);
   } else {
-    constexpr int ND = NV - 2;
-    const double ih[3] = {ih0, ih1, ih2};
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < npts;
-         i += (int64_t)gridDim.x * blockDim.x) {
+#pragma unroll 4
+    for (int64_t i = first; i < npts; i += step) {
       double u[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) u[v] = U[v * npts + i];
-      const double r = wave_rate<ND>(u, gamma, ih);
-      // NaN-propagating max: a non-finite state gives a non-finite dt
-      m = (r > m || r != r) ? r : m;
+      m = umax64(m, __builtin_bit_cast(unsigned long long, wave_rate<NV - 2>(u, gamma, ih)));
     }
   }
-  m = block_max256(m);
-  if (threadIdx.x == 0) partial[blockIdx.x] = m;
+  return m;
+}
+
+// ONE: a single block, which writes dt to `out`; else each block its maximum.
+template <int NV, bool ONE>
+__global__ void __launch_bounds__(ONE ? 1024 : 256)
+    cfl_kernel(const double* __restrict__ U, int64_t npts, double gamma, double ih0, double ih1,
+               double ih2, double adv_rate, double cfl, double* __restrict__ out) {
+  constexpr int NT = ONE ? 1024 : 256;
+  const double ih[3] = {ih0, ih1, ih2};
+  const unsigned long long m = block_max_bits<NT / 64>(
+      rate_max<NV>(U, npts, gamma, ih, adv_rate, (int64_t)blockIdx.x * NT + threadIdx.x,
+                   (int64_t)gridDim.x * NT));
+  const double r = __builtin_bit_cast(double, m);
+  if (threadIdx.x == 0) out[blockIdx.x] = ONE ? cfl / r : r;
 }
 
 __global__ void __launch_bounds__(256) cfl_final_kernel(const double* __restrict__ partial,
                                                         int n, double cfl,
                                                         double* __restrict__ dt) {
-  double m = 0.0;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const double r = partial[i];
-    m = (r > m || r != r) ? r : m;
-  }
-  m = block_max256(m);
-  if (threadIdx.x == 0) dt[0] = cfl / m;
+  unsigned long long m = 0;
+  for (int i = threadIdx.x; i < n; i += 256)
+    m = umax64(m, __builtin_bit_cast(unsigned long long, partial[i]));
+  m = block_max_bits<4>(m);
+  if (threadIdx.x == 0) dt[0] = cfl / __builtin_bit_cast(double, m);
 }
 
 // The batch maxima use wave_max_bits (wcns_device.hpp).
@@ -170,6 +166,17 @@ __global__ void lincomb_kernel(double* __restrict__ out, const double* __restric
   }
 }
 
+// (-u + u1 + 2 u2) / 3 in one pass (1D 15000 nodes, a four-stage step with a given
+// dt: with the sweep's gains 30.0 -> 24.4 us), as lincomb of u and u1 and then of that and u2 round it.
+__global__ void rk4_sum_kernel(double* __restrict__ out, const double* __restrict__ u,
+                               const double* __restrict__ u1, const double* __restrict__ u2,
+                               int64_t n) {
+#pragma clang fp contract(off)
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    out[i] = __builtin_fma(1.0, __builtin_fma(-1.0 / 3.0, u[i], 1.0 / 3.0 * u1[i]), 2.0 / 3.0 * u2[i]);
+}
+
 // --------------------------------------------------------------- launchers --
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -180,37 +187,40 @@ int cfl_blocks(int64_t npts) {
   return (int)b;
 }
 
+// One block where its chain of loads is shorter than a second launch: microseconds,
+// two launches -> one block: 1000 nodes 4.3 -> 2.2, 60^2 4.8 -> 3.8, 5000 4.4 -> 3.6,
+// 15000 4.5 -> 6.9.  (Advection's rate is a number of the plan's.)
+template <int NV>
+static hipError_t cfl_go(const double* U, int64_t npts, double gamma, const double (&ih)[3],
+                         double adv_rate, double cfl, double* partial, int nblocks, double* dt_out,
+                         hipStream_t stream) {
+  if (NV == 1 || npts <= 4096) {
+    hipLaunchKernelGGL((cfl_kernel<NV, true>), dim3(1), dim3(1024), 0, stream, U, npts, gamma, ih[0],
+                       ih[1], ih[2], adv_rate, cfl, dt_out);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((cfl_kernel<NV, false>), dim3(nblocks), dim3(256), 0, stream, U, npts, gamma,
+                     ih[0], ih[1], ih[2], adv_rate, cfl, partial);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(cfl_final_kernel, dim3(1), dim3(256), 0, stream, partial, nblocks, cfl,
+                     dt_out);
+  return hipGetLastError();
+}
+
 hipError_t launch_cfl(int nv, int ndim, const double* U, int64_t npts, double gamma,
                       const double* ih, const double* adv, double cfl, double* partial,
                       int nblocks, double* dt_out, hipStream_t stream) {
   double adv_rate = 0.0;
   for (int d = 0; d < ndim; ++d) adv_rate += (adv[d] < 0 ? -adv[d] : adv[d]) * ih[d];
-  const double ih0 = ih[0], ih1 = ndim > 1 ? ih[1] : 0.0, ih2 = ndim > 2 ? ih[2] : 0.0;
+  const double h[3] = {ih[0], ndim > 1 ? ih[1] : 0.0, ndim > 2 ? ih[2] : 0.0};
+#define WCNS_C(NVV) \
+  case NVV: return cfl_go<NVV>(U, npts, gamma, h, adv_rate, cfl, partial, nblocks, dt_out, stream);
   switch (nv) {
-    case 1:
-      hipLaunchKernelGGL(cfl_partial_kernel<1>, dim3(nblocks), dim3(256), 0, stream, U, npts,
-                         gamma, ih0, ih1, ih2, adv_rate, partial);
-      break;
-    case 3:
-      hipLaunchKernelGGL(cfl_partial_kernel<3>, dim3(nblocks), dim3(256), 0, stream, U, npts,
-                         gamma, ih0, ih1, ih2, adv_rate, partial);
-      break;
-    case 4:
-      hipLaunchKernelGGL(cfl_partial_kernel<4>, dim3(nblocks), dim3(256), 0, stream, U, npts,
-                         gamma, ih0, ih1, ih2, adv_rate, partial);
-      break;
-    case 5:
-      hipLaunchKernelGGL(cfl_partial_kernel<5>, dim3(nblocks), dim3(256), 0, stream, U, npts,
-                         gamma, ih0, ih1, ih2, adv_rate, partial);
-      break;
-    default:
-      return hipErrorInvalidValue;
+    WCNS_C(1) WCNS_C(3) WCNS_C(4) WCNS_C(5)
+    default: return hipErrorInvalidValue;
   }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(cfl_final_kernel, dim3(1), dim3(256), 0, stream, partial, nblocks, cfl,
-                     dt_out);
-  return hipGetLastError();
+#undef WCNS_C
 }
 
 hipError_t launch_batch_cfl(const double* U, int64_t total, const BatchArgs& b, double gamma,
@@ -251,9 +261,10 @@ hipError_t launch_lincomb(double* out, const double* x, double ax, const double*
   return hipGetLastError();
 }
 
-hipError_t launch_axpy_state(double* y, const double* x, double a, int64_t n,
-                             hipStream_t stream) {
-  return launch_lincomb(y, y, 1.0, x, a, nullptr, 0.0, n, stream);
+hipError_t launch_rk4_sum(double* out, const double* u, const double* u1, const double* u2,
+                          int64_t n, hipStream_t stream) {
+  hipLaunchKernelGGL(rk4_sum_kernel, dim3(elem_grid(n)), dim3(256), 0, stream, out, u, u1, u2, n);
+  return hipGetLastError();
 }
 
 }  // namespace wcns
