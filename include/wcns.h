@@ -121,8 +121,8 @@ wcns_status wcns_residual(wcns_plan* plan, const double* U, double* R, void* wor
                           void* stream);
 
 /* *dt_dev = cfl / max_i sum_d (|u_d| + c) / h_d over U (for advection
-   sum_d |a_d| / h_d).  Two deterministic kernels (block maxima, then one
-   block).  Graph-capturable. */
+   sum_d |a_d| / h_d); a non-finite node gives a non-finite dt.  One or two
+   deterministic kernels.  Graph-capturable. */
 wcns_status wcns_cfl_dt(wcns_plan* plan, const double* U, double cfl, double* dt_dev,
                         void* work, void* stream);
 
@@ -136,8 +136,7 @@ wcns_status wcns_rk3_step(wcns_plan* plan, double* U, void* work, const double* 
 
 /* wcns_rk3_step for callers that cannot allocate (code under HIP graph
    capture, tight serving loops, harnesses that forbid allocation): the same
-   step, the same kernels and bitwise the same result, with no workspace
-   argument.  The stage states, the residual accumulator (2D/3D), the CFL
+   step and bitwise the same result, with no workspace argument.  The stage states, the residual accumulator (2D/3D), the CFL
    block maxima and dt live in a device array inside the library, 48 MiB
    per GPU, held until the process ends: the plan must need at most that
    (2 states, 3 in 2D/3D, plus 16.25 KB: a state of up to about 3.1 M

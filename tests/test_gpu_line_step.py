@@ -1,8 +1,8 @@
-"""The one-launch step of short 1D problems: bitwise the sweeps' step (a ragged
-batch of one problem runs on the sweeps), and the oracle's step, around the
-sizes at which it pads to a wavefront, and on both sides of its size limit;
-with a given dt, a CFL-limited one, kept stages, the four-stage scheme, and a
-non-physical state reported."""
+"""The one-launch step of short 1D problems: bitwise the step of a ragged batch of
+one problem and of the sweeps, and the oracle's step, around the sizes at which
+it pads to a wavefront, and on both sides of its size limit; with a given dt, a
+CFL-limited one, kept stages, the four-stage scheme, and a non-physical state
+reported."""
 import numpy as np
 import pytest
 import torch
