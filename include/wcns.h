@@ -109,6 +109,16 @@ void wcns_desc_init(wcns_desc* d);
 wcns_status wcns_plan_create(const wcns_desc* desc, wcns_plan** plan);
 wcns_status wcns_plan_destroy(wcns_plan* plan);
 
+/* A second plan of the same problem, tile shapes and workspace size for a run
+   that is differentiated (destroy it on its own; it does not refer to `plan`
+   afterwards).  The derivative of the FE map amplifies the last bit of the
+   states it is taken at: a change of the steps' rounding moves single entries
+   of a gradient by up to 1e-7 of its rms.  With FE and PFE weights this plan's
+   residual and steps keep one arithmetic for good, at the cost of the shorter
+   one and of the one-launch steps; they differ from `plan`'s by rounding only.
+   Any other plan's calls are unchanged by it: all entry points take it. */
+wcns_status wcns_plan_gradient(const wcns_plan* plan, wcns_plan** gplan);
+
 /* Number of float64 values in one state: nv * nx * ny * nz. */
 int64_t wcns_state_elems(const wcns_plan* plan);
 /* Bytes of device workspace `work` that the calls below need (the caller

@@ -24,7 +24,8 @@ SCHEMES = {"wcns": 0, "weno": 1}
 
 # Every entry point declared in include/wcns.h.
 EXPORTS = [
-    "wcns_desc_init", "wcns_plan_create", "wcns_plan_destroy", "wcns_state_elems",
+    "wcns_desc_init", "wcns_plan_create", "wcns_plan_destroy", "wcns_plan_gradient",
+    "wcns_state_elems",
     "wcns_workspace_bytes", "wcns_residual", "wcns_cfl_dt", "wcns_rk3_step",
     "wcns_rk3_step_noalloc",
     "wcns_rk3_step_stages", "wcns_rk4_step",
@@ -75,6 +76,7 @@ def lib():
         "wcns_desc_init": (None, [C.POINTER(Desc)]),
         "wcns_plan_create": (st, [C.POINTER(Desc), C.POINTER(vp)]),
         "wcns_plan_destroy": (st, [vp]),
+        "wcns_plan_gradient": (st, [vp, C.POINTER(vp)]),
         "wcns_state_elems": (C.c_int64, [vp]),
         "wcns_workspace_bytes": (C.c_size_t, [vp]),
         "wcns_residual": (st, [vp, vp, vp, vp, vp]),

@@ -18,6 +18,7 @@
 
 #include "../../include/wcns.h"
 #include "wcns_internal.hpp"
+#include "wcns_sweep_tile.hpp"
 
 using namespace wcns;
 
@@ -121,7 +122,17 @@ wcns_status validate(const wcns_desc* d, bool batch) {
   return WCNS_OK;
 }
 
+// Elementary symmetric polynomials e[0..n] of x.
+void esym(const long double* x, int n, long double* e) {
+  e[0] = 1.0L;
+  for (int r = 1; r <= n; ++r) e[r] = 0.0L;
+  for (int i = 0; i < n; ++i)
+    for (int r = i + 1; r >= 1; --r) e[r] += x[i] * e[r - 1];
+}
+
 void interp_params(const wcns_desc* d, InterpParams* ip) {
+  ip->plain = 0;
+  ip->Ke = 0.0;
   ip->eps = d->eps;
   ip->xi = d->xi;
   ip->cv = d->cv;
@@ -218,12 +229,6 @@ void interp_params(const wcns_desc* d, InterpParams* ip) {
   const double* fa[3] = {ip->weno ? kV0a : kG0a, ip->weno ? kV1a : kG1a, ip->weno ? kV2a : kG2a};
   const double* fb[3] = {ip->weno ? kV0b : kG0b, ip->weno ? kV1b : kG1b, ip->weno ? kV2b : kG2b};
   const int offd[3] = {0, 3, 7}, offp[3] = {0, 2, 5};
-  auto esym = [](const long double* x, int n, long double* e) {  // e[0..n]
-    e[0] = 1.0L;
-    for (int r = 1; r <= n; ++r) e[r] = 0.0L;
-    for (int i = 0; i < n; ++i)
-      for (int r = i + 1; r >= 1; --r) e[r] += x[i] * e[r - 1];
-  };
   for (int m = 0; m < 3; ++m) {
     const int nt = count[m];
     long double k[4], e[5], ex[5], pa[3] = {0, 0, 0}, pb[3] = {0, 0, 0};
@@ -249,6 +254,44 @@ void interp_params(const wcns_desc* d, InterpParams* ip) {
     for (int r = 0; r < nt - 1; ++r) {
       ip->Pa[offp[m] + r] = (double)pa[r];
       ip->Pb[offp[m] + r] = (double)pb[r];
+    }
+  }
+}
+
+// The map constants of the plain arithmetic (plain::fe_map_poly), in long double
+// from the K_j: elementary symmetric polynomials e_r of a map's K_j for the
+// denominator prod_j (1 + E K_j), and of the K_l, l != j, weighted by -2 a_j and
+// -2 b_j for the numerator.
+void plain_params(InterpParams* ip) {
+  ip->plain = 1;
+  if (!ip->shared_exp) return;
+  const double* fa[3] = {kG0a, kG1a, kG2a};
+  const double* fb[3] = {kG0b, kG1b, kG2b};
+  const int first[3] = {0, 3, 7}, count[3] = {3, 4, 3}, offp[3] = {0, 2, 5};
+  ip->Ke = std::exp(2.0 * ip->xi - ip->C2[0] - ip->C2[1] - ip->C2[2]);
+  for (int m = 0; m < 3; ++m) {
+    const int nt = count[m];
+    long double K[4], e[5], ex[5], pa[4] = {0, 0, 0, 0}, pb[4] = {0, 0, 0, 0};
+    for (int j = 0; j < nt; ++j) K[j] = (long double)ip->K[first[m] + j];
+    esym(K, nt, e);
+    // monic: divided by the leading coefficient prod_j K_j (1 up to rounding)
+    const long double lead = e[nt];
+    for (int r = 1; r < nt; ++r) ip->Pd[first[m] + r - 1] = (double)(e[r] / lead);
+    ip->Pd[first[m] + nt - 1] = (double)(1.0L / lead);
+    for (int j = 0; j < nt; ++j) {
+      long double rest[3];
+      int n = 0;
+      for (int l = 0; l < nt; ++l)
+        if (l != j) rest[n++] = K[l];
+      esym(rest, n, ex);
+      for (int r = 1; r < nt; ++r) {
+        pa[r] += -2.0L * fa[m][j] * ex[r];
+        pb[r] += -2.0L * fb[m][j] * ex[r];
+      }
+    }
+    for (int r = 1; r < nt; ++r) {
+      ip->Pa[offp[m] + r - 1] = (double)(pa[r] / lead);
+      ip->Pb[offp[m] + r - 1] = (double)(pb[r] / lead);
     }
   }
 }
@@ -287,6 +330,8 @@ struct wcns_plan {
   bool one_launch_stages() const {
     return d.scheme == WCNS_SCHEME_WCNS && stage_step_ok(d.ndim, nv, d.n);
   }
+  // the arithmetic of differentiated runs: every step by the sweeps
+  bool plain() const { return spec_plain(sweep_spec_of(ip)); }
 };
 
 struct wcns_batch_plan {
@@ -484,6 +529,20 @@ wcns_status wcns_plan_create(const wcns_desc* desc, wcns_plan** plan) {
   return WCNS_OK;
 }
 
+wcns_status wcns_plan_gradient(const wcns_plan* plan, wcns_plan** gplan) {
+  g_err.clear();
+  if (!plan || !gplan) return fail(WCNS_EINVAL, "NULL argument");
+  *gplan = nullptr;
+  wcns_plan* P = new (std::nothrow) wcns_plan(*plan);
+  if (!P) return fail(WCNS_ENOMEM, "host allocation failed");
+  if (P->d.scheme == WCNS_SCHEME_WCNS) plain_params(&P->ip);
+  // (the other 3D tiles, which keep a field's states in registers, fuse one product
+  // of the back-projection differently)
+  if (P->nv == 5 && sweep_trim(5, P->seg, P->bw)) P->seg = 32, P->bw = 4;
+  *gplan = P;
+  return WCNS_OK;
+}
+
 wcns_status wcns_plan_destroy(wcns_plan* plan) {
   delete plan;
   return WCNS_OK;
@@ -542,7 +601,7 @@ namespace {
 wcns_status line_step(const wcns_plan* P, double* U, double* U1, double* U2, const double* dt_dev,
                       double cfl, double* dtw, int32_t* status_dev, int stages, hipStream_t s,
                       bool* done) {
-  *done = P->d.ndim == 1 && P->d.scheme == WCNS_SCHEME_WCNS &&
+  *done = P->d.ndim == 1 && P->d.scheme == WCNS_SCHEME_WCNS && !P->plain() &&
           line_step_ok(P->nv, P->npts, P->d.diff, stages);
   if (!*done) return WCNS_OK;
   SweepArgs a;
@@ -618,7 +677,7 @@ wcns_status rk3_step_into(wcns_plan* plan, double* U, double* W1, double* W2, vo
   // (stage arrays of the caller's that lie in the workspace meet the residuals there)
   const size_t sb = sizeof(double) * plan->nv * plan->npts;
   const bool inside = keep_stages && (overlaps(W1, sb, work, plan->bytes) || overlaps(W2, sb, work, plan->bytes));
-  if (plan->one_launch_stages() && !inside) {
+  if (plan->one_launch_stages() && !plan->plain() && !inside) {
     if (!dt_dev && !(cfl > 0.0)) return fail(WCNS_EINVAL, "cfl must be > 0 when dt_dev is NULL");
     return stage_step(plan, U, W1, keep_stages ? W2 : nullptr, (double*)(w + plan->off_W2),
                       (double*)(w + plan->off_partial), (double*)(w + plan->off_dt), dt_dev, cfl,
@@ -688,7 +747,7 @@ wcns_status wcns_rk3_step_noalloc(wcns_plan* plan, double* U, const double* dt_d
   if (st != WCNS_OK) return st;
   char* w = (char*)base;
   const size_t state = align256(sizeof(double) * plan->nv * plan->npts);
-  if (plan->one_launch_stages()) {
+  if (plan->one_launch_stages() && !plan->plain()) {
     const size_t op = (1 + 2 * (size_t)plan->d.ndim) * state;
     const size_t od = op + align256(sizeof(double) * plan->npartial);
     if (od + 256 <= kScratchBytes)

@@ -40,16 +40,21 @@ enum : int { WJS = 0, WZ = 1, WFE = 2, WPFE = 3, WLIN = 4 };
 //                 a narrow band around its null points (stair);
 //   SPEC_JS, SPEC_Z  JS weights, Z weights with p = 2;
 //   SPEC_PFE      SPEC_FE's weights outside the band of App. A, Z inside;
-//   SPEC_GENERIC  every choice, from the run-time parameters.
+//   SPEC_GENERIC  every choice, from the run-time parameters;
+//   SPEC_PLAIN_FE, SPEC_PLAIN  FE weights, and FE and PFE weights from the run-time
+//                 parameters, in runs that are differentiated (wcns_plain_device.hpp).
 enum : int {
   SPEC_GENERIC = 0,
   SPEC_FE = 1,
   SPEC_FE_SAT = 2,
   SPEC_JS = 3,
   SPEC_Z = 4,
-  SPEC_PFE = 5
+  SPEC_PFE = 5,
+  SPEC_PLAIN_FE = 6,
+  SPEC_PLAIN = 7
 };
-// Specialisations that read the exponential's table from LDS.
+constexpr bool spec_plain(int spec) { return spec == SPEC_PLAIN_FE || spec == SPEC_PLAIN; }
+// Specialisations that read exp2_tab's table from LDS.
 constexpr bool spec_table(int spec) {
   return spec == SPEC_FE || spec == SPEC_FE_SAT || spec == SPEC_PFE;
 }
@@ -78,6 +83,8 @@ struct InterpParams {
   //     (the coefficients of X^0 vanish);
   // maps at offsets 0, 3, 7 of Pd and 0, 2, 5 of Pa and Pb
   double Pd[10], Pa[7], Pb[7];
+  // (plain: those of plain::fe_map_poly, and its Ke = exp(2 xi - C2[0] - C2[1] - C2[2]))
+  double Ke;
   double kap[10];   // the k_j (the adjoint)
   double xa;        // 2 xi 64 / ln 2 (exp2_tab: fast_fe, stair)
   int xsh;          // the shift of X_0 and X_1 (fast_fe; 0 for stair)
@@ -87,6 +94,7 @@ struct InterpParams {
   int weno;         // 1: K, C2 hold the Table B.2 maps (WENO family)
   int stair;        // 1: shared_exp = 0 and each map's null points increase by
                     //    more than twice the band
+  int plain;        // 1: a run that is differentiated (wcns_plain_device.hpp)
   int fast_fe;      // 1: shared_exp and the unclamped products of the
                     //    SPEC_FE path stay below e^600 (see fe_map_poly)
 };

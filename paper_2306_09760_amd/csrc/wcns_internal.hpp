@@ -40,6 +40,14 @@ inline int spec_of(const InterpParams& ip) {
   return ip.fast_fe ? SPEC_FE : ip.stair ? SPEC_FE_SAT : SPEC_GENERIC;
 }
 
+// The specialisation of a WCNS sweep: of a run that is differentiated the plain one
+// of FE and PFE weights, except where the maps are staircases.
+inline int sweep_spec_of(const InterpParams& ip) {
+  const int s = spec_of(ip);
+  if (!ip.plain || s == SPEC_FE_SAT || (ip.weights != WFE && ip.weights != WPFE)) return s;
+  return s == SPEC_FE ? SPEC_PLAIN_FE : SPEC_PLAIN;
+}
+
 // Arguments of one directional sweep.
 struct SweepArgs {
   const double* U;      // state under the stencil, U^(k)

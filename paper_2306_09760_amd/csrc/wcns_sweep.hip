@@ -63,7 +63,14 @@ template <int NV, int DIR, bool BATCH, int TM, int W>
 static hipError_t sweep_go(const SweepArgs& a, const BatchArgs& b, const TileGeom& g, int mode,
                            hipStream_t s) {
   const size_t lds = sizeof(double) * SweepLayout<NV, TM, W>::lds_doubles;
-  switch (spec_of(a.ip)) {
+  const int spec = sweep_spec_of(a.ip);
+  if constexpr (!BATCH) {
+    if (spec == SPEC_PLAIN_FE)
+      return sweep_launch<NV, DIR, BATCH, SPEC_PLAIN_FE, TM, W>(a, b, g, mode, lds, s);
+    if (spec == SPEC_PLAIN)
+      return sweep_launch<NV, DIR, BATCH, SPEC_PLAIN, TM, W>(a, b, g, mode, lds, s);
+  }
+  switch (spec) {
     case SPEC_FE: return sweep_launch<NV, DIR, BATCH, SPEC_FE, TM, W>(a, b, g, mode, lds, s);
     case SPEC_FE_SAT: return sweep_launch<NV, DIR, BATCH, SPEC_FE_SAT, TM, W>(a, b, g, mode, lds, s);
     case SPEC_JS: return sweep_launch<NV, DIR, BATCH, SPEC_JS, TM, W>(a, b, g, mode, lds, s);

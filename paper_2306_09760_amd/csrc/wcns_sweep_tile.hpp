@@ -38,6 +38,7 @@
 #include <type_traits>
 
 #include "wcns_internal.hpp"
+#include "wcns_plain_device.hpp"
 #include "wcns_sweep_common.hpp"
 
 namespace wcns {
@@ -186,6 +187,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
                                            const TileGeom& g, int mode, int64_t tile,
                                            double* smem) {
   static_assert(!(STEP && BATCH), "a one-launch stage is of one problem");
+  constexpr bool PLAIN = spec_plain(SPEC);
   using L = SweepLayout<NV, TM, W>;
   constexpr int ND = L::ND, NR = L::NR, TN = L::TN, TMW = L::TMW, SV = L::SV;
   constexpr int LW = L::LW, LTMW = L::LTMW;
@@ -325,6 +327,8 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
   double xv = 0.0;
   if constexpr (spec_table(SPEC)) {
     if (tid < 64) xv = exp2_tab_entry(tid, a.ip.xsh);
+  } else if constexpr (SPEC == SPEC_PLAIN_FE) {
+    if (tid < 64) xv = kExp2Tab64[tid];
   }
   if constexpr (STEP) {
     if (in.st > 1) {
@@ -369,11 +373,24 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
       for (int v = 0; v < NV; ++v) sU[v * SV + idx] = buf[it][v];
     }
   }
-  if constexpr (spec_table(SPEC)) {
+  if constexpr (spec_table(SPEC) || SPEC == SPEC_PLAIN_FE) {
     if (tid < 64) sX[tid] = xv;
   }
   __syncthreads();
 
+  // the functions below in the specialisation's arithmetic
+  auto roe = [&](const double* UA, const double* UB) {
+    if constexpr (PLAIN) return plain::roe_average<ND>(UA, UB, a.pp.gamma);
+    else return roe_average<ND>(UA, UB, a.pp.gamma);
+  };
+  auto derived = [&](RoeState<ND>& r) {
+    if constexpr (PLAIN) plain::roe_derived<ND>(r, a.pp.gamma);
+    else roe_derived<ND>(r, a.pp.gamma);
+  };
+  auto interp = [&](const double (&w)[6], double* l, double* r) {
+    if constexpr (PLAIN) plain::interp5_pair<SPEC == SPEC_PLAIN_FE>(a.ip, w, l, r, sX);
+    else interp5_pair<SPEC>(a.ip, w, l, r, sX);
+  };
   // With one midpoint column per lane (TM W = 256), lane q computes the Roe
   // state, all interpolations and the flux of midpoint column q itself, so
   // the Roe, interpolation and flux phases need no barrier between them.
@@ -389,7 +406,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
         UA[v] = u[v * SV];
         UB[v] = u[v * SV + W];
       }
-      rsq = roe_average<ND>(UA, UB, a.pp.gamma);
+      rsq = roe(UA, UB);
     }
   } else if constexpr (NV > 1) {
     if (proj) {
@@ -403,7 +420,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
           UA[v] = u[v * SV];
           UB[v] = u[v * SV + W];
         }
-        const RoeState<ND> rs = roe_average<ND>(UA, UB, a.pp.gamma);
+        const RoeState<ND> rs = roe(UA, UB);
         double* r = sR + q;
 #pragma unroll
         for (int k = 0; k < ND; ++k) r[k * TMW] = rs.vel[k];
@@ -458,9 +475,10 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
             for (int k = 0; k < ND; ++k) rs.vel[k] = r[k * TMW];
             rs.ic = r[(ND + 2) * TMW];
           }
-          roe_derived<ND>(rs, a.pp.gamma);
+          derived(rs);
           double l[NV];
-          field_row<ND, DIR>(rs, v, l);
+          if constexpr (PLAIN) plain::field_row<ND, DIR>(rs, v, l);
+          else field_row<ND, DIR>(rs, v, l);
           project_stencil<NV, SV, W>(u, l, w);
         }
       }
@@ -470,13 +488,13 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
       for (int j = 0; j < 6; ++j) w[j] = uv[j * W];
     }
     if constexpr (TRIM) {
-      interp5_pair<SPEC>(a.ip, w, &wl, &wr, sX);
+      interp(w, &wl, &wr);
       if (v < NV - 1) {
         sW[q] = wl;
         sW[RO * TMW + q] = wr;
       }
     } else {
-      interp5_pair<SPEC>(a.ip, w, sW + q, sW + NV * TMW + q, sX);
+      interp(w, sW + q, sW + NV * TMW + q);
     }
   }
   if constexpr (!OWN) __syncthreads();
@@ -510,7 +528,10 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
     if constexpr (NV == 1) {
       // (twice the upwind flux, as llf_flux2)
       const double uL = sW[q], uR = sW[TMW + q];
-      F[0] = __builtin_fma(a.pp.adv, uL + uR, -__builtin_fabs(a.pp.adv) * (uR - uL));
+      if constexpr (PLAIN)
+        F[0] = 0.5 * a.pp.adv * (uL + uR) - 0.5 * __builtin_fabs(a.pp.adv) * (uR - uL);
+      else
+        F[0] = __builtin_fma(a.pp.adv, uL + uR, -__builtin_fabs(a.pp.adv) * (uR - uL));
     } else {
       double WL[NV], WR[NV], UL[NV], UR[NV];
 #pragma unroll
@@ -527,10 +548,15 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
           rs.H = r[(ND + 0) * TMW];
           rs.c = r[(ND + 1) * TMW];
           rs.ic = r[(ND + 2) * TMW];
-          roe_derived<ND>(rs, a.pp.gamma);
+          derived(rs);
         }
-        unproject<ND, DIR>(rs, WL, UL);
-        unproject<ND, DIR>(rs, WR, UR);
+        if constexpr (PLAIN) {
+          plain::unproject<ND, DIR>(rs, WL, UL);
+          plain::unproject<ND, DIR>(rs, WR, UR);
+        } else {
+          unproject<ND, DIR>(rs, WL, UL);
+          unproject<ND, DIR>(rs, WR, UR);
+        }
       } else {
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
@@ -538,7 +564,8 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
           UR[v] = WR[v];
         }
       }
-      llf_flux2<ND, DIR>(UL, UR, a.pp.gamma, F);
+      if constexpr (PLAIN) plain::llf_flux<ND, DIR>(UL, UR, a.pp.gamma, F);
+      else llf_flux2<ND, DIR>(UL, UR, a.pp.gamma, F);
     }
 #pragma unroll
     for (int v = 0; v < NV; ++v) sW[v * TMW + q] = F[v];
@@ -549,7 +576,8 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
       double Uc[NV], Fc[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) Uc[v] = sU[v * SV + q + 2 * W];
-      node_flux<NV, DIR>(a.pp, Uc, Fc);
+      if constexpr (PLAIN) plain::node_flux<NV, DIR>(a.pp, Uc, Fc);
+      else node_flux<NV, DIR>(a.pp, Uc, Fc);
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         if (TRIM && v >= NV - 2)
@@ -612,9 +640,14 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
         const lds_cptr fv = lds_row(f + v * TMW);
         // F of node t + k + 2 at nf[k W]: nodes t + 3 and t + 5 around t + 4
         const lds_cptr nf = lds_row(tv ? u + v * SV + 2 * W : f + (NV + v) * TMW);
-        const double d = __builtin_fma(
-            0.75, fv[2 * W] - fv[W],
-            __builtin_fma(-0.3, nf[3 * W] - nf[W], (1.0 / 60.0) * (fv[3 * W] - fv[0])));
+        double d;
+        if constexpr (PLAIN)
+          d = 1.5 * (fv[2 * W] - fv[W]) - 0.3 * (nf[3 * W] - nf[W]) +
+              (1.0 / 30.0) * (fv[3 * W] - fv[0]);
+        else
+          d = __builtin_fma(
+              0.75, fv[2 * W] - fv[W],
+              __builtin_fma(-0.3, nf[3 * W] - nf[W], (1.0 / 60.0) * (fv[3 * W] - fv[0])));
         res[v] = -ih * d;
       }
     } else {
@@ -622,9 +655,14 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
       for (int v = 0; v < NV; ++v) {
         Un[v] = u[v * SV + 5 * W];
         const lds_cptr fv = lds_row(f + v * TMW);
-        const double d = __builtin_fma(
-            75.0 / 128.0, fv[3 * W] - fv[2 * W],
-            __builtin_fma(-25.0 / 768.0, fv[4 * W] - fv[W], (3.0 / 1280.0) * (fv[5 * W] - fv[0])));
+        double d;
+        if constexpr (PLAIN)
+          d = (75.0 / 64.0) * (fv[3 * W] - fv[2 * W]) +
+              (-25.0 / 384.0) * (fv[4 * W] - fv[W]) + (3.0 / 640.0) * (fv[5 * W] - fv[0]);
+        else
+          d = __builtin_fma(
+              75.0 / 128.0, fv[3 * W] - fv[2 * W],
+              __builtin_fma(-25.0 / 768.0, fv[4 * W] - fv[W], (3.0 / 1280.0) * (fv[5 * W] - fv[0])));
         res[v] = -ih * d;
       }
     }
@@ -689,7 +727,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
 #define WCNS_REG_WAVES 5
 #endif
 constexpr int sweep_waves(int nv, int tmw, int spec) {
-  return spec == SPEC_GENERIC                ? 1
+  return spec == SPEC_GENERIC || spec == SPEC_PLAIN ? 1
          : spec == SPEC_JS || spec == SPEC_Z ? 6
          : spec == SPEC_FE_SAT               ? (sweep_reg(nv, tmw) ? 4 : 5)
          : sweep_reg(nv, tmw)                ? WCNS_REG_WAVES

@@ -29,6 +29,11 @@ backward pass reverses each step from them (``wcns_rk3_step_adjoint_stages``)
 without any recomputation: memory traded for the two residual evaluations
 per step that the adjoint step otherwise repeats.
 
+The run's steps are those of the plan's gradient plan (``Plan.gradient_plan``):
+with FE and PFE weights single entries of a gradient depend on the last bit of
+the states it is taken at, so a rollout keeps one rounding of its steps for good,
+whichever kernels ``Plan.rk3_step`` uses.
+
 dt is held fixed (a CFL-limited dt depends on the state, and its derivative
 is not part of the step adjoint).  Every step runs on the GPU; this module
 only orders the calls.
@@ -183,6 +188,7 @@ def rollout(plan, U0: torch.Tensor, dt: torch.Tensor, nsteps: int, snapshots: in
     if isinstance(plan, Plan):  # the library's plans check what reaches the kernels
         plan._check_state(U0)
         plan._dt(dt, optional=False)
+        plan = plan.gradient_plan()
     if stages:
         return _StagedRollout.apply(U0, plan, dt, int(nsteps))
     return _Rollout.apply(U0, plan, dt, int(nsteps), int(snapshots))

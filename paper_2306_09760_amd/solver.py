@@ -81,6 +81,17 @@ class Plan:
                 pass
             self._h = None
 
+    def gradient_plan(self):
+        """A plan of the same problem, with this plan's tiles and workspace, for
+        a run that is differentiated: its steps keep one rounding for good
+        (wcns_plan_gradient; rollout uses it)."""
+        h = C.c_void_p()
+        check(lib().wcns_plan_gradient(self._h, C.byref(h)), "wcns_plan_gradient")
+        g = Plan.__new__(Plan)
+        g.__dict__.update(self.__dict__)
+        g._h = h
+        return g
+
     def _check_state(self, U):
         if U.dtype != torch.float64 or not U.is_contiguous() or U.device != self.device:
             raise _lib.WCNSError("state must be a contiguous float64 tensor on the plan's device")
