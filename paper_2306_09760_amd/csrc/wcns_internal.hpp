@@ -25,18 +25,18 @@ enum SweepMode : int { MODE_RES = 0, MODE_ACC = 1, MODE_STAGE = 2, MODE_LIN = 3 
 // exponential where that one's range ends (xi about 990 at kappa = 0.5): two
 // steps of 512 tubes at xi = 995 0.557 -> 0.443 ms, at 1e6 0.479 -> 0.345 ms;
 // 3D 96^3 residual at xi = 1000 0.410 -> 0.326 ms, at 1e6 0.274 -> 0.201 ms.  PFE at
-// such a steepness takes them too (its own switch at run time; eps must leave the
-// squares' product, eps^6, a normal number): WENO 2D 1000 x 993 at xi = 1e6 0.130 ->
-// 0.105 ms.
+// such a steepness takes them too (its own switch at run time): WENO 2D 1000 x 993 at
+// xi = 1e6 0.130 -> 0.105 ms.  FE and the staircases multiply all three squares: eps
+// must leave eps^6 a normal number, or a flat stencil has no weights at all.
 inline int spec_of(const InterpParams& ip) {
   if (ip.weights == WJS) return ip.eps >= 1e-70 ? SPEC_JS : SPEC_GENERIC;
   if (ip.zpow != 2) return SPEC_GENERIC;
   if (ip.weights == WZ) return ip.eps >= 1e-95 ? SPEC_Z : SPEC_GENERIC;
   if (ip.weights == WPFE) {
     if (ip.fast_fe) return ip.eps >= 1e-95 ? SPEC_PFE : SPEC_GENERIC;
-    return ip.stair && ip.eps >= 1e-45 ? SPEC_FE_SAT : SPEC_GENERIC;
+    return ip.stair && ip.eps >= 1e-51 ? SPEC_FE_SAT : SPEC_GENERIC;
   }
-  if (ip.weights != WFE) return SPEC_GENERIC;
+  if (ip.weights != WFE || ip.eps < 1e-51) return SPEC_GENERIC;
   return ip.fast_fe ? SPEC_FE : ip.stair ? SPEC_FE_SAT : SPEC_GENERIC;
 }
 
