@@ -18,7 +18,6 @@
 
 #include "../../include/wcns.h"
 #include "wcns_internal.hpp"
-#include "wcns_sweep_tile.hpp"
 
 using namespace wcns;
 
@@ -536,9 +535,6 @@ wcns_status wcns_plan_gradient(const wcns_plan* plan, wcns_plan** gplan) {
   wcns_plan* P = new (std::nothrow) wcns_plan(*plan);
   if (!P) return fail(WCNS_ENOMEM, "host allocation failed");
   if (P->d.scheme == WCNS_SCHEME_WCNS) plain_params(&P->ip);
-  // (the other 3D tiles, which keep a field's states in registers, fuse one product
-  // of the back-projection differently)
-  if (P->nv == 5 && sweep_trim(5, P->seg, P->bw)) P->seg = 32, P->bw = 4;
   *gplan = P;
   return WCNS_OK;
 }

@@ -383,10 +383,6 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
     if constexpr (PLAIN) return plain::roe_average<ND>(UA, UB, a.pp.gamma);
     else return roe_average<ND>(UA, UB, a.pp.gamma);
   };
-  auto derived = [&](RoeState<ND>& r) {
-    if constexpr (PLAIN) plain::roe_derived<ND>(r, a.pp.gamma);
-    else roe_derived<ND>(r, a.pp.gamma);
-  };
   auto interp = [&](const double (&w)[6], double* l, double* r) {
     if constexpr (PLAIN) plain::interp5_pair<SPEC == SPEC_PLAIN_FE>(a.ip, w, l, r, sX);
     else interp5_pair<SPEC>(a.ip, w, l, r, sX);
@@ -475,7 +471,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
             for (int k = 0; k < ND; ++k) rs.vel[k] = r[k * TMW];
             rs.ic = r[(ND + 2) * TMW];
           }
-          derived(rs);
+          roe_derived<ND>(rs, a.pp.gamma);
           double l[NV];
           if constexpr (PLAIN) plain::field_row<ND, DIR>(rs, v, l);
           else field_row<ND, DIR>(rs, v, l);
@@ -529,7 +525,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
       // (twice the upwind flux, as llf_flux2)
       const double uL = sW[q], uR = sW[TMW + q];
       if constexpr (PLAIN)
-        F[0] = 0.5 * a.pp.adv * (uL + uR) - 0.5 * __builtin_fabs(a.pp.adv) * (uR - uL);
+        F[0] = plain::advection_flux(a.pp.adv, uL, uR);
       else
         F[0] = __builtin_fma(a.pp.adv, uL + uR, -__builtin_fabs(a.pp.adv) * (uR - uL));
     } else {
@@ -548,7 +544,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
           rs.H = r[(ND + 0) * TMW];
           rs.c = r[(ND + 1) * TMW];
           rs.ic = r[(ND + 2) * TMW];
-          derived(rs);
+          roe_derived<ND>(rs, a.pp.gamma);
         }
         if constexpr (PLAIN) {
           plain::unproject<ND, DIR>(rs, WL, UL);
@@ -642,8 +638,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
         const lds_cptr nf = lds_row(tv ? u + v * SV + 2 * W : f + (NV + v) * TMW);
         double d;
         if constexpr (PLAIN)
-          d = 1.5 * (fv[2 * W] - fv[W]) - 0.3 * (nf[3 * W] - nf[W]) +
-              (1.0 / 30.0) * (fv[3 * W] - fv[0]);
+          d = plain::diff_mnd6<W>(fv, nf);
         else
           d = __builtin_fma(
               0.75, fv[2 * W] - fv[W],
@@ -657,8 +652,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
         const lds_cptr fv = lds_row(f + v * TMW);
         double d;
         if constexpr (PLAIN)
-          d = (75.0 / 64.0) * (fv[3 * W] - fv[2 * W]) +
-              (-25.0 / 384.0) * (fv[4 * W] - fv[W]) + (3.0 / 640.0) * (fv[5 * W] - fv[0]);
+          d = plain::diff_md6<W>(fv);
         else
           d = __builtin_fma(
               75.0 / 128.0, fv[3 * W] - fv[2 * W],
