@@ -488,6 +488,44 @@ __device__ __forceinline__ double fe_stair(double w, const double (&a)[NT], cons
   return g;
 }
 
+// The JS or the p = 2 Z weights, up to a factor, with a reciprocal per indicator.  JS,
+// Z, PFE and the staircases take products of the indicators instead (weigh5), which
+// overflow long before the indicators do: from state differences of 1e34 on for JS,
+// 1e45 for Z at eps = 1e-40, 1e51 for PFE, 1e25 for the staircases.  These reach 1e77
+// (Z, PFE and the staircases: tau / eps = 1e154), and a midpoint whose flux is not
+// finite is interpolated again with them (WIDE).  One comparison per midpoint, where
+// one per interpolation kept its indicators in registers: JS, Z, PFE and staircase
+// sweeps within 1-2 % either way (2D 2048^2 Z 0.299 ms against 0.296, at xi = 1e6 0.417
+// against 0.421), per interpolation 1-7 % slower; the short lines' one-launch steps,
+// bound by latency, 4-5 % (201 nodes, Z, 9.7 -> 10.1 us).
+template <bool JS, class FAM>
+__device__ __forceinline__ void wide_weights(double b0, double b1, double b2, double (&z)[3]) {
+#pragma clang fp contract(off)
+  const double r0 = rcp(b0), r1 = rcp(b1), r2 = rcp(b2);
+  if constexpr (JS) {
+    z[0] = r0 * r0;
+    z[1] = FAM::dr1 * (r1 * r1);
+    z[2] = FAM::dr2 * (r2 * r2);
+  } else {
+    const double tau = b0 - b2;
+    const double q0 = tau * r0, q1 = tau * r1, q2 = tau * r2;
+    z[0] = __builtin_fma(q0, q0, 1.0);
+    z[1] = FAM::dr1 * __builtin_fma(q1, q1, 1.0);
+    z[2] = FAM::dr2 * __builtin_fma(q2, q2, 1.0);
+  }
+  const double zi = rcp(z[0] + z[1] + z[2]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) z[k] *= zi;
+}
+// Specialisations with those products.
+constexpr bool spec_narrow(int spec) {
+  return spec == SPEC_JS || spec == SPEC_Z || spec == SPEC_PFE || spec == SPEC_FE_SAT;
+}
+// Not finite (for a NaN in the stencil too, which stays one).
+__device__ __forceinline__ bool overflown(double x) {
+  return __builtin_expect(!(__builtin_fabs(x) <= 1.79769313486231570815e308), 0);
+}
+
 // The nonlinear weights of eq. 11 / 14 (+ FE map, eq. 20; PFE switch) from
 // the regularised smoothness indicators b_k = IS_k + eps (so that
 // tau = |IS_0 - IS_2| = |b_0 - b_2|), applied to the candidates of eq. 5.  The
@@ -506,8 +544,8 @@ __device__ __forceinline__ double fe_stair(double w, const double (&a)[NT], cons
 // 0.366 ms, the 3D 256^3 step 11.27 -> 10.00 ms, a 2D 512^2 WENO-FE step
 // 0.165 -> 0.153 ms (one box, both sides in turn); the value's error against
 // quadruple precision went from 6e-16 to 0.3-1.3e-16 rms.
-// xt: the exp2_tab_entry table in LDS (spec_table only).
-template <int SPEC = SPEC_GENERIC, class FAM = FamWcns>
+// xt: the exp2_tab_entry table in LDS (spec_table only).  WIDE: see wide_weights.
+template <int SPEC = SPEC_GENERIC, class FAM = FamWcns, bool WIDE = false>
 __device__ __forceinline__ double weigh5(const InterpParams& P, double um, double x0, double x1,
                                          double x2, double b0, double b1, double b2,
                                          const double* xt = nullptr) {
@@ -528,7 +566,12 @@ __device__ __forceinline__ double weigh5(const InterpParams& P, double um, doubl
     const double z1 = FAM::dr1 * __builtin_fma(t2, p02, p);
     const double z2 = FAM::dr2 * __builtin_fma(t2, p01, p);
     const double zi = rcp(z0 + z1 + z2);
-    const double w0 = z0 * zi, w1 = z1 * zi, w2 = z2 * zi;
+    double w0 = z0 * zi, w1 = z1 * zi, w2 = z2 * zi;
+    if constexpr (WIDE) {
+      double z[3];
+      wide_weights<false, FAM>(b0, b1, b2, z);
+      w0 = z[0], w1 = z[1], w2 = z[2];
+    }
     if constexpr (SPEC == SPEC_FE) return fe_mean<FAM>(P, w0, w1, w2, um, x0, x1, x2, xt);
     if (P.weights == WPFE && __builtin_fabs(w0 - FAM::d0) <= P.cv &&
         __builtin_fabs(w1 - FAM::d1) <= P.cv && __builtin_fabs(w2 - FAM::d2) <= P.cv)
@@ -540,6 +583,11 @@ __device__ __forceinline__ double weigh5(const InterpParams& P, double um, doubl
     const double g2 = fe_stair<3>(w2, FAM::g2a(), FAM::g2b(), P.K + 7, P, xt);
     const double ginv = rcp(g0 + g1 + g2);
     return __builtin_fma(FAM::scale * ginv, __builtin_fma(g0, x0, __builtin_fma(g1, x1, g2 * x2)), um);
+  }
+  if constexpr (WIDE && (SPEC == SPEC_JS || SPEC == SPEC_Z)) {
+    double w[3];
+    wide_weights<SPEC == SPEC_JS, FAM>(b0, b1, b2, w);
+    return __builtin_fma(FAM::scale, __builtin_fma(w[0], x0, __builtin_fma(w[1], x1, w[2] * x2)), um);
   }
   if constexpr (SPEC == SPEC_JS) {
     // alpha_k = d_k / b_k^2 times b_0^2 b_1^2 b_2^2: no reciprocal but the sum's
@@ -561,7 +609,12 @@ __device__ __forceinline__ double weigh5(const InterpParams& P, double um, doubl
       const double num = __builtin_fma(z0, x0, __builtin_fma(z1, x1, z2 * x2));
       return __builtin_fma(FAM::scale * num, zi, um);
     }
-    const double w0 = z0 * zi, w1 = z1 * zi, w2 = z2 * zi;
+    double w0 = z0 * zi, w1 = z1 * zi, w2 = z2 * zi;
+    if constexpr (WIDE) {
+      double z[3];
+      wide_weights<false, FAM>(b0, b1, b2, z);
+      w0 = z[0], w1 = z[1], w2 = z[2];
+    }
     if (__builtin_fabs(w0 - FAM::d0) <= P.cv && __builtin_fabs(w1 - FAM::d1) <= P.cv &&
         __builtin_fabs(w2 - FAM::d2) <= P.cv)
       return __builtin_fma(FAM::scale, __builtin_fma(w0, x0, __builtin_fma(w1, x1, w2 * x2)), um);
@@ -619,7 +672,7 @@ __device__ __forceinline__ double weigh5(const InterpParams& P, double um, doubl
 // With s_k the second difference of sub-stencil k and f_k its parabola's
 // slope at u_2 (d_1 + s_0 / 2, d_1 + s_1 / 2, d_2 - s_2 / 2), IS_k = f_k^2 + s_k^2 and the candidate is the parabola's
 // value at the midpoint, u_2 + f_k / 2 + s_k / 8 = u_2 + (4 f_k + s_k) / 8.
-template <int SPEC = SPEC_GENERIC>
+template <int SPEC = SPEC_GENERIC, bool WIDE = false>
 __device__ __forceinline__ void interp5_pair(const InterpParams& P, const double (&u)[6],
                                              double* left, double* right,
                                              const double* xt = nullptr) {
@@ -642,12 +695,12 @@ __device__ __forceinline__ void interp5_pair(const InterpParams& P, const double
   }
   // IS_k + eps = f_k^2 + (s_k^2 + eps)
   const double q1 = __builtin_fma(s1, s1, P.eps), q2 = __builtin_fma(s2, s2, P.eps);
-  *left = weigh5<SPEC>(P, u[2], x0, x1, x2,
-                       __builtin_fma(f0, f0, __builtin_fma(s0, s0, P.eps)),
-                       __builtin_fma(f1, f1, q1), __builtin_fma(f2, f2, q2), xt);
-  *right = weigh5<SPEC>(P, u[3], y0, y1, y2,
-                        __builtin_fma(g0, g0, __builtin_fma(s3, s3, P.eps)),
-                        __builtin_fma(g1, g1, q2), __builtin_fma(g2, g2, q1), xt);
+  *left = weigh5<SPEC, FamWcns, WIDE>(P, u[2], x0, x1, x2,
+                                      __builtin_fma(f0, f0, __builtin_fma(s0, s0, P.eps)),
+                                      __builtin_fma(f1, f1, q1), __builtin_fma(f2, f2, q2), xt);
+  *right = weigh5<SPEC, FamWcns, WIDE>(P, u[3], y0, y1, y2,
+                                       __builtin_fma(g0, g0, __builtin_fma(s3, s3, P.eps)),
+                                       __builtin_fma(g1, g1, q2), __builtin_fma(g2, g2, q1), xt);
 }
 
 // ----------------------------------------- WENO5 reconstruction (App. B) --
@@ -679,7 +732,7 @@ struct FamWeno {
 // weno5 through the specialised paths of weigh5 (Table B.1 ideal weights, Table
 // B.2 maps); xt: the exp2_tab_entry table in LDS.  With f_k and s_k as in interp5_pair, B_k = f_k^2 + 13/12 s_k^2 and
 // the candidate is c + f_k / 2 + s_k / 12.  eps: added to the B_k.
-template <int SPEC>
+template <int SPEC, bool WIDE = false>
 __device__ __forceinline__ double weno5_spec(const InterpParams& P, double eps, double a, double b,
                                              double c, double e, double f, const double* xt) {
   constexpr double k = 13.0 / 12.0;
@@ -687,7 +740,7 @@ __device__ __forceinline__ double weno5_spec(const InterpParams& P, double eps, 
   const double s0 = d1 - d0, s1 = d2 - d1, s2 = d3 - d2;
   const double f0 = __builtin_fma(0.5, s0, d1), f1 = __builtin_fma(0.5, s1, d1),
                f2 = __builtin_fma(-0.5, s2, d2);
-  return weigh5<SPEC, FamWeno>(P, c, __builtin_fma(6.0, f0, s0), __builtin_fma(6.0, f1, s1),
+  return weigh5<SPEC, FamWeno, WIDE>(P, c, __builtin_fma(6.0, f0, s0), __builtin_fma(6.0, f1, s1),
                                __builtin_fma(6.0, f2, s2),
                                __builtin_fma(f0, f0, __builtin_fma(k * s0, s0, eps)),
                                __builtin_fma(f1, f1, __builtin_fma(k * s1, s1, eps)),

@@ -157,6 +157,30 @@ __global__ void __launch_bounds__(1024) line_step_kernel(LineArgs a) {
         __syncthreads();
       }
     }
+    // the six values of field v around midpoint q
+    auto stencil = [&](int v, int q, double (&w)[6]) {
+      const double* u = sU + q;
+      if (proj) {
+        if constexpr (NV > 1) {
+          RoeState<ND> rs;
+          rs.vel[0] = sR[q];
+          rs.ic = sR[3 * NM + q];
+          roe_derived<ND>(rs, a.pp.gamma);
+          double l[NV];
+          field_row<ND, 0>(rs, v, l);
+#pragma unroll
+          for (int j = 0; j < 6; ++j) {
+            double t = l[0] * u[j];
+#pragma unroll
+            for (int e = 1; e < NV; ++e) t = __builtin_fma(l[e], u[e * SU + j], t);
+            w[j] = t;
+          }
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 6; ++j) w[j] = u[v * SU + j];
+      }
+    };
     // one task = 64 midpoints of one field
     const int nw = NM >> 6;
 #pragma unroll 1
@@ -164,28 +188,8 @@ __global__ void __launch_bounds__(1024) line_step_kernel(LineArgs a) {
       const int v = NV == 1 ? 0 : (k >= nw) + (k >= 2 * nw);
       const int q = ((k - v * nw) << 6) + (tid & 63);
       if (q < mids) {
-        const double* u = sU + q;
         double w[6];
-        if (proj) {
-          if constexpr (NV > 1) {
-            RoeState<ND> rs;
-            rs.vel[0] = sR[q];
-            rs.ic = sR[3 * NM + q];
-            roe_derived<ND>(rs, a.pp.gamma);
-            double l[NV];
-            field_row<ND, 0>(rs, v, l);
-#pragma unroll
-            for (int j = 0; j < 6; ++j) {
-              double t = l[0] * u[j];
-#pragma unroll
-              for (int e = 1; e < NV; ++e) t = __builtin_fma(l[e], u[e * SU + j], t);
-              w[j] = t;
-            }
-          }
-        } else {
-#pragma unroll
-          for (int j = 0; j < 6; ++j) w[j] = u[v * SU + j];
-        }
+        stencil(v, q, w);
         interp5_pair<SPEC>(a.ip, w, sW + v * NM + q, sW + (NV + v) * NM + q, sX);
       }
     }
@@ -194,27 +198,39 @@ __global__ void __launch_bounds__(1024) line_step_kernel(LineArgs a) {
 #pragma unroll 1
     for (int q = tid; q < mids; q += lanes) {
       double F[NV];
-      if constexpr (NV == 1) {
-        const double uL = sW[q], uR = sW[NM + q];
-        F[0] = __builtin_fma(a.pp.adv, uL + uR, -__builtin_fabs(a.pp.adv) * (uR - uL));
-      } else {
-        double WL[NV], WR[NV], UL[NV], UR[NV];
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          UL[v] = WL[v] = sW[v * NM + q];
-          UR[v] = WR[v] = sW[(NV + v) * NM + q];
+      for (int pass = 0; pass < (spec_narrow(SPEC) ? 2 : 1); ++pass) {  // (as in sweep_tile)
+        if constexpr (NV == 1) {
+          const double uL = sW[q], uR = sW[NM + q];
+          F[0] = __builtin_fma(a.pp.adv, uL + uR, -__builtin_fabs(a.pp.adv) * (uR - uL));
+        } else {
+          double WL[NV], WR[NV], UL[NV], UR[NV];
+#pragma unroll
+          for (int v = 0; v < NV; ++v) {
+            UL[v] = WL[v] = sW[v * NM + q];
+            UR[v] = WR[v] = sW[(NV + v) * NM + q];
+          }
+          if (proj) {
+            RoeState<ND> rs;
+            rs.vel[0] = sR[q];
+            rs.H = sR[NM + q];
+            rs.c = sR[2 * NM + q];
+            rs.ic = sR[3 * NM + q];
+            roe_derived<ND>(rs, a.pp.gamma);
+            unproject<ND, 0>(rs, WL, UL);
+            unproject<ND, 0>(rs, WR, UR);
+          }
+          llf_flux2<ND, 0>(UL, UR, a.pp.gamma, F);
         }
-        if (proj) {
-          RoeState<ND> rs;
-          rs.vel[0] = sR[q];
-          rs.H = sR[NM + q];
-          rs.c = sR[2 * NM + q];
-          rs.ic = sR[3 * NM + q];
-          roe_derived<ND>(rs, a.pp.gamma);
-          unproject<ND, 0>(rs, WL, UL);
-          unproject<ND, 0>(rs, WR, UR);
+        if (!spec_narrow(SPEC) || pass > 0 || !overflown(F[NV - 1])) break;
+        if constexpr (spec_narrow(SPEC)) {
+#pragma unroll 1
+          for (int v = 0; v < NV; ++v) {
+            double w[6];
+            stencil(v, q, w);
+            interp5_pair<SPEC, true>(a.ip, w, sW + v * NM + q, sW + (NV + v) * NM + q, sX);
+          }
         }
-        llf_flux2<ND, 0>(UL, UR, a.pp.gamma, F);
       }
 #pragma unroll
       for (int v = 0; v < NV; ++v) sW[v * NM + q] = F[v];

@@ -170,12 +170,9 @@ __global__ void __launch_bounds__(kPackLanes) __attribute__((amdgpu_waves_per_eu
       for (int v = 0; v < NV; ++v) sF[v * TM + q] = Fc[v];
     }
     __syncthreads();
-    // one field of one midpoint per task, as in the sweeps
-#pragma unroll 1
-    for (int k = tid; k < NV * TM; k += tid < TM ? NV * TM : TM) {
-      const int v = __builtin_amdgcn_readfirstlane(k >> 7), q = k & (TM - 1);
+    // the six values of field v around midpoint q
+    auto stencil = [&](int v, int q, double (&w)[6]) {
       const double* u = sU + q;
-      double w[6];
       if (proj) {
         RoeState<ND> rs;
         rs.vel[0] = sR[q];
@@ -188,27 +185,47 @@ __global__ void __launch_bounds__(kPackLanes) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
         for (int j = 0; j < 6; ++j) w[j] = u[v * TN + j];
       }
+    };
+    // one field of one midpoint per task, as in the sweeps
+#pragma unroll 1
+    for (int k = tid; k < NV * TM; k += tid < TM ? NV * TM : TM) {
+      const int v = __builtin_amdgcn_readfirstlane(k >> 7), q = k & (TM - 1);
+      double w[6];
+      stencil(v, q, w);
       interp5_pair<SPEC>(a.ip, w, sW + v * TM + q, sW + (NV + v) * TM + q, sX);
     }
     __syncthreads();
     if (tid < TM) {  // twice the midpoint flux
-      double WL[NV], WR[NV], UL[NV], UR[NV], F[NV];
+      double F[NV];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        UL[v] = WL[v] = sW[v * TM + tid];
-        UR[v] = WR[v] = sW[(NV + v) * TM + tid];
+      for (int pass = 0; pass < (spec_narrow(SPEC) ? 2 : 1); ++pass) {  // (as in sweep_tile)
+        double WL[NV], WR[NV], UL[NV], UR[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          UL[v] = WL[v] = sW[v * TM + tid];
+          UR[v] = WR[v] = sW[(NV + v) * TM + tid];
+        }
+        if (proj) {
+          RoeState<ND> rs;
+          rs.vel[0] = sR[tid];
+          rs.H = sR[TM + tid];
+          rs.c = sR[2 * TM + tid];
+          rs.ic = sR[3 * TM + tid];
+          roe_derived<ND>(rs, a.pp.gamma);
+          unproject<ND, 0>(rs, WL, UL);
+          unproject<ND, 0>(rs, WR, UR);
+        }
+        llf_flux2<ND, 0>(UL, UR, a.pp.gamma, F);
+        if (!spec_narrow(SPEC) || pass > 0 || !overflown(F[NV - 1])) break;
+        if constexpr (spec_narrow(SPEC)) {
+#pragma unroll 1
+          for (int v = 0; v < NV; ++v) {
+            double w[6];
+            stencil(v, tid, w);
+            interp5_pair<SPEC, true>(a.ip, w, sW + v * TM + tid, sW + (NV + v) * TM + tid, sX);
+          }
+        }
       }
-      if (proj) {
-        RoeState<ND> rs;
-        rs.vel[0] = sR[tid];
-        rs.H = sR[TM + tid];
-        rs.c = sR[2 * TM + tid];
-        rs.ic = sR[3 * TM + tid];
-        roe_derived<ND>(rs, a.pp.gamma);
-        unproject<ND, 0>(rs, WL, UL);
-        unproject<ND, 0>(rs, WR, UR);
-      }
-      llf_flux2<ND, 0>(UL, UR, a.pp.gamma, F);
 #pragma unroll
       for (int v = 0; v < NV; ++v) sW[v * TM + tid] = F[v];
     }

@@ -428,15 +428,9 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
     }
   }
 
-  double wl = 0.0, wr = 0.0;  // TRIM: the last field's states
-  // one field of one midpoint per task: its left- and right-biased
-  // interpolations share the six projected stencil values
-#pragma unroll 1
-  for (int q = tid; q < NV * TMW; q += NT) {
-    const int v = q >> LTMW;
-    const int rem = q & (TMW - 1);  // = m W + c
-    const double* u = sU + rem;     // node m of column c; node m + j at u[j W]
-    double w[6];
+  // the six values of field v around midpoint rem = m W + c
+  auto stencil = [&](int v, int rem, double (&w)[6]) {
+    const double* u = sU + rem;  // node m of column c; node m + j at u[j W]
     if (proj) {
       if constexpr (NV > 1) {
         const double* r = sR + rem;
@@ -483,6 +477,16 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
 #pragma unroll
       for (int j = 0; j < 6; ++j) w[j] = uv[j * W];
     }
+  };
+
+  double wl = 0.0, wr = 0.0;  // TRIM: the last field's states
+  // one field of one midpoint per task: its left- and right-biased
+  // interpolations share the six projected stencil values
+#pragma unroll 1
+  for (int q = tid; q < NV * TMW; q += NT) {
+    const int v = q >> LTMW;
+    double w[6];
+    stencil(v, q & (TMW - 1), w);
     if constexpr (TRIM) {
       interp(w, &wl, &wr);
       if (v < NV - 1) {
@@ -521,47 +525,67 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
 #pragma unroll 1
   for (int q = tid; q < TMW; q += NT) {
     double F[NV];
-    if constexpr (NV == 1) {
-      // (twice the upwind flux, as llf_flux2)
-      const double uL = sW[q], uR = sW[TMW + q];
-      if constexpr (PLAIN)
-        F[0] = plain::advection_flux(a.pp.adv, uL, uR);
-      else
-        F[0] = __builtin_fma(a.pp.adv, uL + uR, -__builtin_fabs(a.pp.adv) * (uR - uL));
-    } else {
-      double WL[NV], WR[NV], UL[NV], UR[NV];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        WL[v] = TRIM && v == NV - 1 ? wl : sW[v * TMW + q];
-        WR[v] = TRIM && v == NV - 1 ? wr : sW[(RO + v) * TMW + q];
-      }
-      if (proj) {
-        RoeState<ND> rs = rsq;
-        if constexpr (!REG) {
-          const double* r = sR + q;
-#pragma unroll
-          for (int k = 0; k < ND; ++k) rs.vel[k] = r[k * TMW];
-          rs.H = r[(ND + 0) * TMW];
-          rs.c = r[(ND + 1) * TMW];
-          rs.ic = r[(ND + 2) * TMW];
-          roe_derived<ND>(rs, a.pp.gamma);
-        }
-        if constexpr (PLAIN) {
-          plain::unproject<ND, DIR>(rs, WL, UL);
-          plain::unproject<ND, DIR>(rs, WR, UR);
-        } else {
-          unproject<ND, DIR>(rs, WL, UL);
-          unproject<ND, DIR>(rs, WR, UR);
-        }
+    for (int pass = 0; pass < (spec_narrow(SPEC) ? 2 : 1); ++pass) {
+      if constexpr (NV == 1) {
+        // (twice the upwind flux, as llf_flux2)
+        const double uL = sW[q], uR = sW[TMW + q];
+        if constexpr (PLAIN)
+          F[0] = plain::advection_flux(a.pp.adv, uL, uR);
+        else
+          F[0] = __builtin_fma(a.pp.adv, uL + uR, -__builtin_fabs(a.pp.adv) * (uR - uL));
       } else {
+        double WL[NV], WR[NV], UL[NV], UR[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-          UL[v] = WL[v];
-          UR[v] = WR[v];
+          WL[v] = TRIM && v == NV - 1 ? wl : sW[v * TMW + q];
+          WR[v] = TRIM && v == NV - 1 ? wr : sW[(RO + v) * TMW + q];
+        }
+        if (proj) {
+          RoeState<ND> rs = rsq;
+          if constexpr (!REG) {
+            const double* r = sR + q;
+#pragma unroll
+            for (int k = 0; k < ND; ++k) rs.vel[k] = r[k * TMW];
+            rs.H = r[(ND + 0) * TMW];
+            rs.c = r[(ND + 1) * TMW];
+            rs.ic = r[(ND + 2) * TMW];
+            roe_derived<ND>(rs, a.pp.gamma);
+          }
+          if constexpr (PLAIN) {
+            plain::unproject<ND, DIR>(rs, WL, UL);
+            plain::unproject<ND, DIR>(rs, WR, UR);
+          } else {
+            unproject<ND, DIR>(rs, WL, UL);
+            unproject<ND, DIR>(rs, WR, UR);
+          }
+        } else {
+#pragma unroll
+          for (int v = 0; v < NV; ++v) {
+            UL[v] = WL[v];
+            UR[v] = WR[v];
+          }
+        }
+        if constexpr (PLAIN) plain::llf_flux<ND, DIR>(UL, UR, a.pp.gamma, F);
+        else llf_flux2<ND, DIR>(UL, UR, a.pp.gamma, F);
+      }
+      // (the last component depends on every field)
+      if (!spec_narrow(SPEC) || pass > 0 || !overflown(F[NV - 1])) break;
+      if constexpr (spec_narrow(SPEC)) {
+#pragma unroll 1
+        for (int v = 0; v < NV; ++v) {
+          double w[6], l, r;
+          stencil(v, q, w);
+          interp5_pair<SPEC, true>(a.ip, w, &l, &r, sX);
+          if (TRIM && v == NV - 1) {
+            wl = l;
+            wr = r;
+          } else {
+            sW[v * TMW + q] = l;
+            sW[(RO + v) * TMW + q] = r;
+          }
         }
       }
-      if constexpr (PLAIN) plain::llf_flux<ND, DIR>(UL, UR, a.pp.gamma, F);
-      else llf_flux2<ND, DIR>(UL, UR, a.pp.gamma, F);
     }
 #pragma unroll
     for (int v = 0; v < NV; ++v) sW[v * TMW + q] = F[v];

@@ -35,6 +35,8 @@
 // sW[NV][128] | the exp table.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "wcns_internal.hpp"
 #include "wcns_sweep_common.hpp"
 
@@ -186,9 +188,10 @@ __global__ void __launch_bounds__(128 * GR) __attribute__((amdgpu_waves_per_eu(w
     }
   }
 
-  // reconstruction of each field at the lane's midpoint
-#pragma unroll 1
-  for (int v = grp; v < NV; v += GR) {
+  // reconstruction of field v at the lane's midpoint, f+^ + f-^ (wide: std::true_type
+  // for wide_weights)
+  auto recon = [&](int v, auto wide) {
+    constexpr bool WIDE = decltype(wide)::value;
     double wp[5], wm[5];  // F + alpha U of nodes 0 .. 4, F - alpha U of nodes 5 .. 1
     if constexpr (NV == 1) {
       const double sp = a.pp.adv + __builtin_fabs(a.pp.adv);
@@ -252,18 +255,29 @@ __global__ void __launch_bounds__(128 * GR) __attribute__((amdgpu_waves_per_eu(w
         wm[j] = __builtin_fma(-al, wu[5 - j], wf[5 - j]);
       }
     }
-    double r;
     if constexpr (SPEC != SPEC_GENERIC)
-      r = weno5_spec<SPEC>(a.ip, eps4, wp[0], wp[1], wp[2], wp[3], wp[4], sX) +
-          weno5_spec<SPEC>(a.ip, eps4, wm[0], wm[1], wm[2], wm[3], wm[4], sX);
+      return weno5_spec<SPEC, WIDE>(a.ip, eps4, wp[0], wp[1], wp[2], wp[3], wp[4], sX) +
+             weno5_spec<SPEC, WIDE>(a.ip, eps4, wm[0], wm[1], wm[2], wm[3], wm[4], sX);
     else
-      r = weno5(a.ip, eps4, wp[0], wp[1], wp[2], wp[3], wp[4]) +
-          weno5(a.ip, eps4, wm[0], wm[1], wm[2], wm[3], wm[4]);
-    sW[v * TMW + mid] = r;
-  }
+      return weno5(a.ip, eps4, wp[0], wp[1], wp[2], wp[3], wp[4]) +
+             weno5(a.ip, eps4, wm[0], wm[1], wm[2], wm[3], wm[4]);
+  };
+#pragma unroll 1
+  for (int v = grp; v < NV; v += GR) sW[v * TMW + mid] = recon(v, std::false_type{});
 
   // twice the midpoint flux, 2 F~ = R (f+^ + f-^), of the lane's own midpoint
   if constexpr (GR > 1) __syncthreads();
+  if constexpr (spec_narrow(SPEC)) {
+    if (grp == 0) {
+      double s = sW[mid];
+#pragma unroll
+      for (int v = 1; v < NV; ++v) s += sW[v * TMW + mid];
+      if (overflown(s)) {
+#pragma unroll 1
+        for (int v = 0; v < NV; ++v) sW[v * TMW + mid] = recon(v, std::true_type{});
+      }
+    }
+  }
   if constexpr (NV > 1) {
     if (proj && grp == 0) {
       double Gv[NV], F[NV];
