@@ -59,6 +59,13 @@ __device__ __forceinline__ void line_combine(bool lin, double ca, double cb, dou
   }
 }
 
+// (-u + u1 + 2 u2) / 3 of the four-stage scheme as rk4_sum_kernel rounds it: with u
+// and u1 (st = 0), then with that and u2.
+__device__ __forceinline__ double rk4_partial(int st, double a, double y) {
+#pragma clang fp contract(off)
+  return st == 0 ? __builtin_fma(-1.0 / 3.0, a, 1.0 / 3.0 * y) : a + 2.0 / 3.0 * y;
+}
+
 template <int NV, int SPEC>
 __global__ void __launch_bounds__(1024) line_step_kernel(LineArgs a) {
   constexpr int ND = NV > 1 ? NV - 2 : 1;
@@ -277,8 +284,7 @@ __global__ void __launch_bounds__(1024) line_step_kernel(LineArgs a) {
                          u0, uk, res, y);
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-          if (st == 0) acc[v] = __builtin_fma(-1.0 / 3.0, u0[v], 1.0 / 3.0 * y[v]);
-          if (st == 1) acc[v] = __builtin_fma(1.0, acc[v], 2.0 / 3.0 * y[v]);
+          if (st < 2) acc[v] = rk4_partial(st, st == 0 ? u0[v] : acc[v], y[v]);
         }
       } else {
         // (-u + u1 + 2 u2)/3 + u3/3 + dt/6 L(u3)
