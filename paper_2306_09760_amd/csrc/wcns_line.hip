@@ -304,8 +304,9 @@ __global__ void __launch_bounds__(1024) line_step_kernel(LineArgs a) {
 }
 
 // --------------------------------------------------------------- launchers --
-// One node per lane, one workgroup's 64 KB of LDS (Euler: about 600 nodes), and
-// short enough that one CU's latency beats the launches it saves.  Microseconds
+// One node per lane, one workgroup's 64 KB of LDS (Euler: 573 nodes with MND6, 571 with
+// MD6, the limit of the four-stage step), and short enough that one CU's latency
+// beats the launches it saves.  Microseconds
 // per step, launches of the sweeps against one launch (FE, xi = 100; one box):
 // Euler SSP-RK3, CFL-limited, 60 nodes 22.3 -> 12.4, 201 21.2 -> 16.2, 300 21.6
 // -> 19.4, 400 21.7 -> 22.5; four stages 60 32.0 -> 15.7, 201 32.8 -> 20.2, 400
@@ -314,7 +315,8 @@ __global__ void __launch_bounds__(1024) line_step_kernel(LineArgs a) {
 // line for Euler is drawn where the FE step breaks even.
 bool line_step_ok(int nv, int64_t n, int diff, int stages) {
   if (nv == 1) return n <= 1024;
-  return nv == 3 && n <= (stages == 3 ? 320 : 600) && line_lds(nv, (int)n, diff) <= 64 * 1024;
+  if (nv != 3 || n > 1024) return false;
+  return (stages == 4 || n <= 320) && line_lds(nv, (int)n, diff) <= 64 * 1024;
 }
 
 hipError_t launch_line_step(int nv, const SweepArgs& s, double* U, double* U1, double* U2,
