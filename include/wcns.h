@@ -344,15 +344,19 @@ wcns_status wcns_probe_copy(const double* src, double* dst, int64_t n, void* str
    method, |z| <= 708), e^z by Cody-Waite reduction and a degree-13 Taylor
    polynomial (|z| <= 708), 1/x to full precision and with one Newton step
    from the hardware seed (x normal), and the square root of 0 or of x in
-   [2^-760, inf).  These are the exponentials, reciprocals and square roots
-   of the residual (Sec. 2, eq. 20; the Roe average and the fluxes).
+   [2^-760, inf), and e^(200 z) as the FE maps take it at xi = 100 (|z| <= 1:
+   the 2^(k/64) table and a degree-4 polynomial).  These are the exponentials,
+   reciprocals and square roots of the residual (Sec. 2, eq. 20; the Roe
+   average and the fluxes): the last of the FE, PFE and staircase kernels, the
+   Cody-Waite one of the run-time weights, Tang's of a gradient plan.
    WCNS_EINVAL for a NULL pointer, n < 0 or an unknown fn. */
 typedef enum {
   WCNS_MATH_EXP_TAB = 0,
   WCNS_MATH_EXP_CW = 1,
   WCNS_MATH_RCP = 2,
   WCNS_MATH_RCP1 = 3,
-  WCNS_MATH_SQRT = 4
+  WCNS_MATH_SQRT = 4,
+  WCNS_MATH_EXP_MAP = 6   /* (5 is unknown) */
 } wcns_math_fn;
 wcns_status wcns_probe_math(const double* x, double* out, int64_t n, int32_t fn, void* stream);
 

@@ -53,13 +53,14 @@ __global__ void probe_copy_tail_kernel(const double* __restrict__ src, double* _
 }
 
 // out[i] = f(x[i]) for the elementary function f selected by fn (0 exp_tab,
-// 1 exp_cw, 2 rcp, 3 rcp1, 4 sqrt_pos), grid-stride; exp_tab reads the
-// 2^(k/64) table from LDS as the sweep kernels do.
+// 1 exp_cw, 2 rcp, 3 rcp1, 4 sqrt_pos, 6 exp2_tab at xi = 100), grid-stride; exp_tab
+// and exp2_tab read their tables from LDS as the sweep kernels do.
 __global__ void __launch_bounds__(256) probe_math_kernel(const double* __restrict__ x,
                                                          double* __restrict__ out, int64_t n,
                                                          int fn) {
   __shared__ double sX[64];
-  if (threadIdx.x < 64) sX[threadIdx.x] = kExp2Tab64[threadIdx.x];
+  if (threadIdx.x < 64)
+    sX[threadIdx.x] = fn == 6 ? exp2_tab_entry(threadIdx.x, 0) : kExp2Tab64[threadIdx.x];
   __syncthreads();
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
@@ -70,6 +71,7 @@ __global__ void __launch_bounds__(256) probe_math_kernel(const double* __restric
       case 1: y = exp_cw(v); break;
       case 2: y = rcp(v); break;
       case 3: y = rcp1(v); break;
+      case 6: y = exp2_tab(v, 0x1.2089fc709fe57p+14, sX); break;  // 2 * 100 * 64 / ln 2
       default: y = sqrt_pos(v); break;
     }
     out[i] = y;
