@@ -598,7 +598,7 @@ wcns_status line_step(const wcns_plan* P, double* U, double* U1, double* U2, con
                       double cfl, double* dtw, int32_t* status_dev, int stages, hipStream_t s,
                       bool* done) {
   *done = P->d.ndim == 1 && P->d.scheme == WCNS_SCHEME_WCNS && !P->plain() &&
-          line_step_ok(P->nv, P->npts, P->d.diff, stages);
+          line_step_ok(P->nv, P->npts, P->d.diff, stages, P->ip);
   if (!*done) return WCNS_OK;
   SweepArgs a;
   sweep_common(P, 0, &a);
@@ -1122,7 +1122,7 @@ wcns_status wcns_batch_plan_create(const wcns_desc* proto, int64_t nprob, const 
   {
     const int G = pack_tile_ghosts(proto->diff), TL = pack_tile_nodes(proto->diff);
     const int64_t nt = batch_tiles(B, G, TL);
-    if (nt <= pack_max_tiles()) {
+    if (nt <= pack_max_tiles(B->ip, 2)) {
       st = batch_tile_tables(B, G, TL, nt, &B->d_pack_p0, &B->d_pack_p1);
       if (st != WCNS_OK) return cleanup(st);
       B->pack_tiles = (int32_t)nt;
@@ -1326,10 +1326,15 @@ static wcns_status batch_pack_steps(wcns_batch_plan* B, double* U, void* work, d
   return WCNS_OK;
 }
 
+// Whether a call's steps are the one-launch steps; the others are their bits.
+static bool pack_serves(const wcns_batch_plan* B, int nsteps) {
+  return B->pack_tiles > 0 && B->pack_tiles <= pack_max_tiles(B->ip, nsteps);
+}
+
 // One step in place.
 static wcns_status batch_one_step(wcns_batch_plan* B, double* U, void* work, double* t_dev,
                                   double t_end, double cfl, int32_t* status, hipStream_t s) {
-  if (B->pack_tiles > 0) return batch_pack_steps(B, U, work, t_dev, t_end, cfl, 1, status, s);
+  if (pack_serves(B, 1)) return batch_pack_steps(B, U, work, t_dev, t_end, cfl, 1, status, s);
   return batch_step_enqueue(B, U, work, t_dev, t_end, cfl, status, s);
 }
 
@@ -1341,7 +1346,7 @@ static wcns_status batch_rk3_steps(wcns_batch_plan* B, double* U, void* work, do
   if (!std::isfinite(t_end)) return fail(WCNS_EINVAL, "t_end must be finite");
   if (nsteps < 0) return fail(WCNS_EINVAL, "nsteps %d < 0", nsteps);
   hipStream_t s = (hipStream_t)stream;
-  if (B->pack_tiles > 0 && cap == 0)
+  if (pack_serves(B, nsteps) && cap == 0)
     return batch_pack_steps(B, U, work, t_dev, t_end, cfl, nsteps, status_dev, s);
   for (int32_t k = 0; k < nsteps; ++k) {
     const wcns_status st = batch_step_enqueue(B, U, work, t_dev, t_end, cfl, status_dev, s, k > 0,

@@ -48,6 +48,13 @@ inline int sweep_spec_of(const InterpParams& ip) {
   return s == SPEC_FE ? SPEC_PLAIN_FE : SPEC_PLAIN;
 }
 
+// FE and PFE maps at run time: a task is several times the work of any other
+// weights', most of it one dependent chain, and where the chip has enough of them the
+// sweeps hide that better than the one-launch steps do (line_step_ok, pack_max_tiles).
+inline bool run_time_maps(const InterpParams& ip) {
+  return spec_of(ip) == SPEC_GENERIC && (ip.weights == WFE || ip.weights == WPFE);
+}
+
 // Arguments of one directional sweep.
 struct SweepArgs {
   const double* U;      // state under the stencil, U^(k)
@@ -162,7 +169,7 @@ hipError_t launch_lincomb(double* out, const double* x, double ax, const double*
 // sweep's arguments (n, bc, diff, ih, ip, pp, status); dt null: cfl / max rate
 // (advection: adv_rate), left in *dt_out; U1, U2: the RK3 stage states' arrays or
 // null; stages: 3 (SSP-RK3) or 4 (eq. 16).
-bool line_step_ok(int nv, int64_t n, int diff, int stages);
+bool line_step_ok(int nv, int64_t n, int diff, int stages, const InterpParams& ip);
 hipError_t launch_line_step(int nv, const SweepArgs& s, double* U, double* U1, double* U2,
                             const double* dt, double cfl, double adv_rate, double* dt_out,
                             int stages, hipStream_t stream);
@@ -201,7 +208,8 @@ struct PackDt {
   unsigned long long* clear;  // cleared for the next step's maxima, may be null
   int32_t* nlive;             // cleared for a rebuild of the live list, may be null
 };
-int64_t pack_max_tiles();
+// The most windows a call of `nsteps` steps is served with.
+int64_t pack_max_tiles(const InterpParams& ip, int nsteps);
 int pack_tile_nodes(int diff);
 int pack_tile_ghosts(int diff);
 hipError_t launch_pack_step(const SweepArgs& s, const BatchArgs& b, const PackDt& d,

@@ -313,9 +313,16 @@ __global__ void __launch_bounds__(1024) line_step_kernel(LineArgs a) {
 // 34.6 -> 28.4, 500 34.7 -> 28.6; Z weights 201 21.8 -> 11.6, 500 21.4 -> 15.8;
 // advection with a given dt, 200 nodes 13.4 -> 8.4, 1000 13.5 -> 11.8.  The RK3
 // line for Euler is drawn where the FE step breaks even.
-bool line_step_ok(int nv, int64_t n, int diff, int stages) {
+// FE maps at run time keep three of four wavefronts of a SIMD busy up to 256
+// midpoints (xi = 500, RK3 253 nodes 28.9 -> 25.6, four stages 44.2 -> 33.4); the
+// fourth costs what the launches do (254 nodes 26.7 -> 30.9, 38.2 -> 40.3; 320 26.6
+// -> 36.0, 38.1 -> 47.0; 573 four stages 38.9 -> 59.3).  PFE interpolates most
+// midpoints without its maps and gains throughout (320 27.6 -> 27.1, 39.6 -> 35.1; 573
+// 40.1 -> 33.9).
+bool line_step_ok(int nv, int64_t n, int diff, int stages, const InterpParams& ip) {
   if (nv == 1) return n <= 1024;
   if (nv != 3 || n > 1024) return false;
+  if (ip.weights == WFE && run_time_maps(ip) && line_mids((int)n, diff) > 256) return false;
   return (stages == 4 || n <= 320) && line_lds(nv, (int)n, diff) <= 64 * 1024;
 }
 

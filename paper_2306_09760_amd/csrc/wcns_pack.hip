@@ -282,7 +282,16 @@ __global__ void __launch_bounds__(kPackLanes) __attribute__((amdgpu_waves_per_eu
 // 42.5, Z 31.8 -> 23.1, 36.5 -> 33.2; 128 (2600) FE 53.5 -> 47.2, 66.1 -> 64.7; 192
 // (3880) FE 69.8 -> 63.8, 82.2 -> 84.7, Z 54.0 -> 48.5, 59.5 -> 63.7; 512 FE 147.6 ->
 // 145.6, 165 -> 171.
-int64_t pack_max_tiles() { return 3072; }
+//
+// With FE and PFE maps at run time (116 registers, four wavefronts to a SIMD) up to four
+// windows per CU, and three where a single step pays for the copy back (xi = 500,
+// sweeps -> here, per call of four steps and of one): 20 tubes of 2000 nodes (367
+// windows) FE 148 -> 132, 42.9 -> 41.3; 3000 of 9 (909) 193 -> 186, 52.0 -> 53.6;
+// 400 of 200 (823) 182 -> 175, 48.2 -> 51.1, PFE 185 -> 184, 49.2 -> 53.8; 2000 of
+// 50 (1358) FE 247 -> 267, 58 -> 71, PFE 248 -> 271, 59 -> 72.
+int64_t pack_max_tiles(const InterpParams& ip, int nsteps) {
+  return !run_time_maps(ip) ? 3072 : nsteps > 1 ? 1024 : 768;
+}
 int pack_tile_nodes(int diff) { return kPackTN - 6 * (diff ? 5 : 4); }
 int pack_tile_ghosts(int diff) { return 3 * (diff ? 5 : 4); }
 
