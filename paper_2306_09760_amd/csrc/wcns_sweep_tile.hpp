@@ -438,9 +438,12 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
           const int ax = tangential_axis<ND, DIR>(v - 2);
           double va;
           if constexpr (REG) {
-            va = rsq.vel[0];
+            // (from a copy: a choice among members behind a reference is taken as one of
+            // their addresses, and the Roe state then goes to scratch)
+            const RoeState<ND> rz = rsq;
+            va = rz.vel[0];
 #pragma unroll
-            for (int k = 1; k < ND; ++k) va = (ax == k) ? rsq.vel[k] : va;
+            for (int k = 1; k < ND; ++k) va = (ax == k) ? rz.vel[k] : va;
           } else {
             va = r[ax * TMW];
           }

@@ -209,9 +209,12 @@ __global__ void __launch_bounds__(128 * GR) __attribute__((amdgpu_waves_per_eu(w
       if (proj) {
         if (v >= 2 && v < NV - 1) {  // shear field: X_ax - vel_ax X_rho
           const int ax = tangential_axis<ND, DIR>(v - 2);
-          double va = rsq.vel[0];
+          // (from a copy: a choice among members behind a reference is taken as one of
+          // their addresses, and the Roe state then goes to scratch)
+          const RoeState<ND> rz = rsq;
+          double va = rz.vel[0];
 #pragma unroll
-          for (int k = 1; k < ND; ++k) va = (ax == k) ? rsq.vel[k] : va;
+          for (int k = 1; k < ND; ++k) va = (ax == k) ? rz.vel[k] : va;
 #pragma unroll
           for (int j = 0; j < 6; ++j) {
             wu[j] = __builtin_fma(-va, u[j * W], u[(1 + ax) * SV + j * W]);
