@@ -122,7 +122,9 @@ wcns_status wcns_plan_gradient(const wcns_plan* plan, wcns_plan** gplan);
 /* Number of float64 values in one state: nv * nx * ny * nz. */
 int64_t wcns_state_elems(const wcns_plan* plan);
 /* Bytes of device workspace `work` that the calls below need (the caller
-   allocates it; 256-byte aligned). */
+   allocates it; 256-byte aligned): a few states and block partials.  Small 3D
+   Euler plans (scheme WCNS, at most 2^18 nodes), whose SSP-RK3 steps take one
+   launch per stage, need two states more than larger ones. */
 size_t wcns_workspace_bytes(const wcns_plan* plan);
 
 /* R = L(U): one residual evaluation (all directions).  U and R must not
@@ -146,12 +148,14 @@ wcns_status wcns_rk3_step(wcns_plan* plan, double* U, void* work, const double* 
 
 /* wcns_rk3_step for callers that cannot allocate (code under HIP graph
    capture, tight serving loops, harnesses that forbid allocation): the same
-   step and bitwise the same result, with no workspace argument.  The stage states, the residual accumulator (2D/3D), the CFL
-   block maxima and dt live in a device array inside the library, 48 MiB
-   per GPU, held until the process ends: the plan must need at most that
-   (2 states, 3 in 2D/3D, plus 16.25 KB: a state of up to about 3.1 M
-   doubles in 1D and 2.1 M in 2D/3D), else WCNS_EINVAL before anything is
-   enqueued.
+   step and bitwise the same result, with no workspace argument.  The stage
+   states, the residual accumulator (2D/3D), the CFL block maxima and dt live
+   in a device array inside the library, 48 MiB per GPU, held until the
+   process ends: the plan must need at most that (2 states, 3 in 2D/3D, plus
+   16.25 KB: a state of up to about 3.1 M doubles in 1D and 2.1 M in 2D/3D),
+   else WCNS_EINVAL before anything is enqueued.  (The steps of a small grid
+   take one launch per stage where the array holds the larger workspace that
+   this needs, and the sweeps' launches otherwise.)
    The call allocates nothing (no hipMalloc, no hipFree; the first call on a
    device looks up the array's address there).  Every call on one GPU uses
    the same array: calls that overlap on the device (two streams, two host
@@ -222,7 +226,12 @@ wcns_status wcns_rk3_step_adjoint_stages(wcns_plan* plan, const double* Un, cons
 /* Measures the candidate tile shapes of this plan's kernels on U (timed with
    HIP events; synchronises the stream) and keeps the fastest in the plan and
    in a per-process cache keyed by shape.  U is not modified.  A WENO plan
-   has one compiled shape: the call returns WCNS_OK and changes nothing. */
+   has one compiled shape: the call returns WCNS_OK and changes nothing.
+   Tile shapes act wherever a plan's sweeps run, every residual among them.
+   Steps of small problems have launches of their own with fixed tiles, which
+   neither this call nor wcns_plan_set_tiles changes: SSP-RK3 steps of 2D and 3D Euler
+   grids of at most 2^17 and 2^18 nodes, and both schemes' steps of short 1D
+   problems (at most a few hundred nodes for Euler, 1024 for advection). */
 wcns_status wcns_plan_autotune(wcns_plan* plan, const double* U, void* work, void* stream);
 /* Current tile shapes: [0] midpoints per tile of the x sweep (128 or 256);
    [1], [2] midpoints along the line and adjacent x-columns per tile of the
@@ -258,7 +267,12 @@ wcns_status wcns_batch_residual(wcns_batch_plan* plan, const double* U, double* 
    state went non-physical) is stopped where it is: dt_p = 0, t_dev[p]
    unchanged, bit 0 of *status_dev set.  The stage kernels take only the
    tiles of problems with dt_p > 0 (a list that the step builds in `work`
-   after computing dt_p), so finished problems cost nothing.
+   after computing dt_p), so finished problems cost nothing.  Small batches
+   (about 330 000 nodes with 24 more per problem; with FE or PFE maps that
+   neither share their exponential nor are staircases, a quarter to a third of
+   that) take a whole step in one launch over every tile instead, whose work on
+   a finished problem is a copy of its state; the tile chosen with
+   wcns_batch_set_tile or wcns_batch_autotune does not act on those steps.
    With wcns_batch_set_graph(plan, 1) the step's kernels are captured into
    a HIP graph on first use (for the given pointers and scalars) and
    replayed afterwards. */
