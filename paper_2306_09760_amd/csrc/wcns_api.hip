@@ -171,9 +171,10 @@ void interp_params(const wcns_desc* d, InterpParams* ip) {
         b += softplus(2.0 * d->xi * ((m == i ? 1.0 : 0.0) - nu[first[m] + j]));
     B = std::max(B, b);
   }
-  // (The line of the path's earlier form, which took the third variable as a
-  // quotient of exponentials that had to stay normal; implied by B < 600 at
-  // the default kappa.)
+  // E_0, E_0 E_1 and Ke = E_0 E_1 E_2 stay normal numbers: the gradient plan's
+  // arithmetic takes the third map's variable as Ke / (E_0 E_1).  (Implied by B < 600
+  // at the default kappa, and one line for every plan, so that a plan and its gradient
+  // plan take the same maps.)
   const bool prod_ok = 2.0 * d->xi < 650.0 && 2.0 * d->xi * (c[0] + c[1]) < 650.0 &&
                        std::fabs(2.0 * d->xi * (1.0 - c[0] - c[1] - c[2])) < 650.0;
   for (int m = 0; m < 3; ++m) {
