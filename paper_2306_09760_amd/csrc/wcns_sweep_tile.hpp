@@ -735,15 +735,19 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const BatchArgs& 
   }
 }
 
-// The FE specialisation runs at six waves per SIMD: the compiler keeps it
-// within 80 VGPRs without spilling, and the largest tile (NV = 3, 256
-// midpoints, 27.3 KB of LDS) still fits six workgroups in a CU's 160 KB.
-// The register path runs at five (at most 102 VGPRs; 86-90 used, no spills):
-// at six its Roe state spills, and LDS allows five 5-variable tiles per CU
-// against three before.
-// The generic interpolation needs ~110 VGPRs and is left unconstrained
-// (capped at 80 it spills); the saturating FE one (SPEC_FE_SAT) needs ~118
-// and runs at four.
+// Waves per SIMD that the compiler must leave room for, by specialisation (vector
+// registers of the Euler kernels; the register path is that of 256-midpoint tiles with
+// 4 and 5 variables):
+//   FE, PFE, PLAIN_FE  six off the register path (FE 70-80, PFE 65-78); the 16x8 and
+//            32x4 y and z tiles of 5 variables spill two registers there in FE and
+//            PLAIN_FE.  Five on it (FE 87-95, PFE 75-91, no spill): at six the Roe state
+//            spills, and the LDS of 5-variable tiles holds five workgroups on a CU.
+//   JS, Z    six throughout (56-80); the 5-variable register path spills up to 16
+//            registers for it, which costs what a wave fewer does (128^3 residual, six
+//            and five waves: Z 0.331 and 0.334 ms, JS 0.305 and 0.306).
+//   FE_SAT   five off the register path (90-96; 4 spilled in the 16x8 and 32x4 z tiles),
+//            four on it (98-116).
+//   run-time weights, PLAIN  unconstrained: 106-128, four waves (capped at 80 they spill).
 #ifndef WCNS_REG_WAVES
 #define WCNS_REG_WAVES 5
 #endif
