@@ -35,11 +35,12 @@
 // carries the same one for every tile.  (Five wavefronts per workgroup
 // leave a CU two workgroups: the first SIMD takes two wavefronts of each.
 // 36 % slower than four.)
-// What bounds it: FP64 VALU issue (76 % of the slots in the 2D kernels) and
-// the serial length of a tile.  With 256 lanes for every system and every
-// per-midpoint phase on the first of four wavefronts, that wavefront issued
-// about 1700 vector instructions per tile and the others 700, and the SIMDs
-// issued in 55 % of their slots.
+// What bounds it: FP64 VALU issue and the serial length of a tile.  The SIMDs issue
+// in 72-75 % of the slots of the cycles their CU is busy in the 2D kernels and 66 %
+// in the 3D ones (SQ_INSTS_VALU / SQ_BUSY_CU_CYCLES; 1024^2: 59-60 % of the slots of
+// 2.4 GHz, at an engine clock of 2.12-2.15 GHz).  With 256 lanes for every system and
+// every per-midpoint phase on the first of four wavefronts, that wavefront issued
+// about 1700 vector instructions per tile and the others 700, and the share was 55 %.
 // Measured (one box, both sides in turn): residual adjoint 60 x 72 x 81 0.317
 // -> 0.248 ms; 2D 1024^2, x and y sweep 0.206 and 0.198 -> 0.165 and 0.168 ms,
 // two differentiable steps with their reverse 3.00 -> 2.51 ms (2.84 with the
