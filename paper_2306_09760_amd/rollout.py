@@ -188,7 +188,7 @@ def rollout(plan, U0: torch.Tensor, dt: torch.Tensor, nsteps: int, snapshots: in
     if isinstance(plan, Plan):  # the library's plans check what reaches the kernels
         plan._check_state(U0)
         plan._dt(dt, optional=False)
-        plan = plan.gradient_plan()
+        plan = plan._rollout_plan()
     if stages:
         return _StagedRollout.apply(U0, plan, dt, int(nsteps))
     return _Rollout.apply(U0, plan, dt, int(nsteps), int(snapshots))

@@ -122,3 +122,41 @@ def test_plan_and_gradient_plan_live_apart(mods):
     assert torch.equal(h.residual(to_dev(state((61, 58)))), a)
     d = np.linalg.norm(to_host(a) - ref) / np.linalg.norm(ref)
     assert 0 < d <= 1e-13
+
+
+def test_rollout_of_a_subclass_calls_its_methods(mods):
+    solver, rollout = mods
+    calls = []
+
+    class Counted(solver.Plan):
+        def rk3_step(self, *a, **kw):
+            calls.append("step")
+            return super().rk3_step(*a, **kw)
+
+        def rk3_step_adjoint(self, *a, **kw):
+            calls.append("adjoint")
+            return super().rk3_step_adjoint(*a, **kw)
+
+    P = Counted(ndim=1, n=(201,), h=(1 / 64,))
+    U = to_dev(state((201,))).requires_grad_()
+    dt = torch.full((1,), 1e-3, dtype=torch.float64, device="cuda")
+    V = rollout.rollout(P, U, dt, 2, 2)
+    V.sum().backward()
+    assert calls.count("step") >= 2 and calls.count("adjoint") == 2
+
+
+def test_rollouts_follow_the_plan(mods):
+    """The gradient plan kept for rollouts takes the plan's tiles and whatever was
+    set on the plan since the rollout before."""
+    solver, rollout = mods
+    P = solver.Plan(ndim=2, n=(61, 58), h=(1 / 64, 1 / 64))
+    g = P._rollout_plan()
+    assert P._rollout_plan() is g and g.tiles == P.tiles == (128, 32, 4)
+    P.tiles = (256, 32, 8)
+    k = P._rollout_plan()
+    assert k is not g and k.tiles == (256, 32, 8) and g.tiles == (128, 32, 4)
+    P.work = torch.empty_like(P.work)
+    assert P._rollout_plan() is k and k.work is P.work
+    P.autotune(to_dev(state((61, 58))))
+    assert P._rollout_plan() is not k and P._rollout_plan().tiles == P.tiles
+    assert P.gradient_plan()._rollout is None and k._h.value != P._h.value
